@@ -323,7 +323,7 @@ int bs_attn_plan_export(int op, const bs_dims* dims, const int32_t* cu_seqlens_q
 enum {
   BS_KERNEL_PLAN = 0,       /* the three planning kernels of a plan */
   BS_KERNEL_FWD = 1,        /* forward attention kernel */
-  BS_KERNEL_PREPROCESS = 2, /* backward preprocess (D = rowsum(dO * O)) */
+  BS_KERNEL_PREPROCESS = 2, /* none (D = rowsum(dO * O) is formed by the dQ kernels) */
   BS_KERNEL_BWD_DQ = 3,     /* backward kernel producing dQ */
   BS_KERNEL_BWD_DKDV = 4,   /* backward kernel producing dK and dV */
   BS_KERNEL_FINALIZE = 5,   /* float32 dQ accumulator -> dq */

@@ -28,11 +28,13 @@ enum PlanKind { kPlanFwd = 0, kPlanBwd = 1 };
 // over key tiles of kFwdBN keys; the backward walks key tiles of kBwdBN keys over
 // query tiles of bwd_bm(head_dim) rows: 96 at head_dim 128, 64 at head_dim 64 (a
 // 96-row tile of 64-wide rows is 12 copy instructions, which 8 waves cannot share
-// evenly).  The float32 kernels use their own sizes.
+// evenly).  The float32 kernels use their own sizes: 64 queries over 128-key tiles, and 32
+// keys over 128-query tiles.
 constexpr int kFwdBM = 128, kFwdBN = 64;
 constexpr int kBwdBN = 128;
 __host__ __device__ constexpr int bwd_bm(int head_dim) { return head_dim == 128 ? 96 : 64; }
-constexpr int kF32BM = 64, kF32BN = 64;
+constexpr int kF32BM = 64, kF32BN = 128;
+constexpr int kF32BwdBN = 32, kF32BwdBM = 128;
 
 // Workspace header: status word and item count, then the per-segment item
 // offsets (segment order) and first slots (list order), the ordered work list,
@@ -47,8 +49,7 @@ struct WsHeader {
 // on; the forward and dQ kernels do so for every segment.
 constexpr int kHeadMajorRowsDkdv = 16384;
 
-// Work item and head of this workgroup in a grid of n_items * n_heads blocks; false when it
-// has none.  Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), so with
+// Work item and head of block b of a grid of n_items * n_heads blocks; false when it has none.  Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), so with
 // n_heads a multiple of 8 each XCD owns the hx = n_heads / 8 heads x*hx .. x*hx+hx-1 and walks
 // the list segment by segment.  Inside a segment's run its heads are interleaved item by
 // item, except where the segment streams at least min_rows rows and the XCD's heads read
@@ -56,11 +57,10 @@ constexpr int kHeadMajorRowsDkdv = 16384;
 // stream): there the XCD walks one head's items at a time, so that the workgroups resident
 // on it read one stream, not hx / heads_per_stream, and each tile of it comes into the
 // XCD's L2 that many times less often.
-__device__ __forceinline__ bool block_work(const WsHeader* __restrict__ hdr,
+__device__ __forceinline__ bool block_work(int b, const WsHeader* __restrict__ hdr,
                                            const WorkItem* __restrict__ items, int n_heads,
                                            int heads_per_stream, int min_rows, WorkItem& it,
                                            int& head) {
-  const int b = blockIdx.x;
   const int n_items = hdr->n_items;
   if ((n_heads & 7) != 0) {
     const int i = b / n_heads;
@@ -92,7 +92,6 @@ struct WsLayout {
   size_t seg_dst;     // int32[num_seqs]
   size_t sorted;      // WorkItem[max_items]
   size_t dvec;        // float[hq * T]      (backward: rowsum(dO * O))
-  size_t dq_acc;      // float[T * hq * d]  (varlen backward only)
   size_t total;
   int64_t max_items;
 };
@@ -279,7 +278,7 @@ hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, co
                            const FwdMerge* merge, const void* ws, const WsLayout& L,
                            hipStream_t stream);
 // The bf16 dQ kernel also forms D = rowsum(dO * O) and stores it in dvec for the dK/dV
-// kernel (the float32 path computes D in launch_bwd_preprocess).
+// kernel.
 hipError_t launch_dq_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                           const void* out, const void* dout, const float* lse, float* dvec,
                           int causal, float scale, void* dq, float* dq_acc, const void* ws,
@@ -292,20 +291,18 @@ hipError_t launch_dkdv_bf16(const bs_dims& dims, const void* q, const void* k, c
 hipError_t launch_fwd_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
                           int causal, float scale, void* out, float* lse, const FwdMerge* merge,
                           const void* ws, const WsLayout& L, hipStream_t stream);
-hipError_t launch_bwd_f32_dq(const bs_dims& dims, const void* q, const void* k, const void* v,
-                             const float* lse, const void* dout, const float* dvec, int causal,
-                             float scale, float* dq_acc, const void* ws, const WsLayout& L,
-                             hipStream_t stream);
-hipError_t launch_bwd_f32_dkdv(const bs_dims& dims, const void* q, const void* k, const void* v,
-                               const float* lse, const void* dout, const float* dvec, int causal,
-                               float scale, void* dk, void* dv, int kv_accumulate,
-                               const void* ws, const WsLayout& L, hipStream_t stream);
+// dq written (dq_accumulate == 0) or added into; like the bf16 kernel it stores D in dvec.
+hipError_t launch_dq_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
+                         const void* out, const void* dout, const float* lse, float* dvec,
+                         int causal, float scale, void* dq, int dq_accumulate, const void* ws,
+                         const WsLayout& L, hipStream_t stream);
+hipError_t launch_dkdv_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
+                           const void* dout, const float* lse, const float* dvec, int causal,
+                           float scale, void* dk, void* dv, int kv_accumulate, const void* ws,
+                           const WsLayout& L, hipStream_t stream);
 
-hipError_t launch_bwd_preprocess(const bs_dims& dims, const void* out, const void* dout,
-                                 float* dvec, float* dq_acc_to_zero, const void* ws,
-                                 hipStream_t stream);
 hipError_t launch_dq_finalize(const bs_dims& dims, const float* dq_acc, void* dq,
-                              const void* ws, hipStream_t stream);
+                              hipStream_t stream);
 hipError_t launch_lse_merge(const bs_dims& dims, const void* out_parts, const float* lse_parts,
                             int32_t n, void* out, float* lse, hipStream_t stream);
 }  // namespace bs

@@ -135,7 +135,7 @@ int plans_of(int op, const bs_dims& d, PlanCfg out[2]) {
     out[1] = PlanCfg{kPlanBwd, kBwdBN, bwd_bm(d.head_dim)};
   } else {
     out[0] = PlanCfg{kPlanFwd, kF32BM, kF32BN};
-    out[1] = PlanCfg{kPlanBwd, kF32BN, kF32BM};
+    out[1] = PlanCfg{kPlanBwd, kF32BwdBN, kF32BwdBM};
   }
   return is_bwd(op) ? 2 : 1;
 }
@@ -197,10 +197,10 @@ WsLayout layout_of(int op, const bs_dims& d, int64_t nseg) {
   if (is_bwd(op)) {
     L.dvec = off;
     off += align256(sizeof(float) * (size_t)(d.hq * d.total_q));
-    if (writes_dq(op) && d.dtype == BS_F32) {  // the float32 dQ kernel accumulates
-      L.dq_acc = off;
+    // the float32 varlen backward's size has room for a dQ accumulator (unused: its dQ kernel
+    // writes dq itself, as the bf16 one does)
+    if (writes_dq(op) && d.dtype == BS_F32)
       off += align256(sizeof(float) * (size_t)(d.total_q * d.hq * d.head_dim));
-    }
   }
   L.total = off;
   L.max_items = mi;
@@ -338,7 +338,6 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   char* base = static_cast<char*>(ws);
   float* dvec = reinterpret_cast<float*>(base + L.dvec);
   const bool f32 = d.dtype == BS_F32;
-  float* acc = direct ? (f32 ? reinterpret_cast<float*>(base + L.dq_acc) : nullptr) : dq_accum;
   WsLayout Lp;
   {
     ProfScope ps(BS_KERNEL_PLAN, s);
@@ -346,19 +345,15 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
                     causal, ws, L, &Lp, s),
            "planner launch");
   }
-  if (f32) {  // the bf16 dQ kernel forms D itself
-    ProfScope ps(BS_KERNEL_PREPROCESS, s);
-    BS_HIP(launch_bwd_preprocess(d, out, dout, dvec, direct ? acc : nullptr, ws, s),
-           "preprocess launch");
-  }
   {
     ProfScope ps(BS_KERNEL_BWD_DQ, s);
     if (f32)
-      BS_HIP(launch_bwd_f32_dq(d, q, k, v, lse, dout, dvec, causal, scale, acc, ws, Lp, s),
+      BS_HIP(launch_dq_f32(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : dq_accum,
+                           !direct, ws, Lp, s),
              "backward dQ launch");
     else
       BS_HIP(launch_dq_bf16(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : nullptr,
-                            acc, ws, Lp, s),
+                            dq_accum, ws, Lp, s),
              "backward dQ launch");
   }
   {
@@ -370,17 +365,13 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   {
     ProfScope ps(BS_KERNEL_BWD_DKDV, s);
     if (f32)
-      BS_HIP(launch_bwd_f32_dkdv(d, q, k, v, lse, dout, dvec, causal, scale, dk, dv, kv_accumulate,
-                                 ws, Lp, s),
+      BS_HIP(launch_dkdv_f32(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate, ws,
+                             Lp, s),
              "backward dK/dV launch");
     else
       BS_HIP(launch_dkdv_bf16(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate,
                               ws, Lp, s),
              "backward dK/dV launch");
-  }
-  if (direct && f32) {
-    ProfScope ps(BS_KERNEL_FINALIZE, s);
-    BS_HIP(launch_dq_finalize(d, acc, dq, ws, s), "dQ finalize launch");
   }
   return ok();
 }
@@ -546,7 +537,7 @@ int bs_dq_finalize(const bs_dims* dims, const float* dq_accum, void* dq, void* s
   BS_TRY(check_ptr(dq_accum, qn, "dq_accum"));
   BS_TRY(check_ptr(dq, qn, "dq"));
   ProfScope ps(BS_KERNEL_FINALIZE, static_cast<hipStream_t>(stream));
-  BS_HIP(launch_dq_finalize(*dims, dq_accum, dq, nullptr, static_cast<hipStream_t>(stream)),
+  BS_HIP(launch_dq_finalize(*dims, dq_accum, dq, static_cast<hipStream_t>(stream)),
          "dQ finalize launch");
   return ok();
 }

@@ -1,4 +1,4 @@
-// Bandwidth-bound row kernels: LSE merge, backward preprocess, dQ finalize.
+// Bandwidth-bound row kernels: LSE merge, dQ finalize.
 //
 // Each (token, head) row of head_dim elements is handled by a group of
 // head_dim/8 (bf16) or head_dim/4 (fp32) lanes, one 16-byte vector per lane,
@@ -86,44 +86,9 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const T* __restrict__ pa
   if (part == 0) lse[(int64_t)h * total_q + t] = m == -INFINITY ? -INFINITY : m + logf(wsum);
 }
 
-// D = rowsum(dO * O) in fp32, stored [hq, T]; optionally zeroes a dQ accumulator.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void preprocess_kernel(const T* __restrict__ o,
-                                                         const T* __restrict__ dout, int64_t rows,
-                                                         int32_t hq, int64_t total_q,
-                                                         float* __restrict__ dvec,
-                                                         float* __restrict__ dq_acc,
-                                                         const WsHeader* __restrict__ hdr) {
-  typedef typename Vec<T>::type V;
-  if (hdr != nullptr && hdr->status != BS_DEV_OK) return;  // planner rejected the input
-  constexpr int LPR = D / Vec<T>::N;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t row = gid / LPR;
-  const int part = gid % LPR;
-  const bool live = row < rows;
-  float s = 0.f;
-  if (live) {
-    const V a = *reinterpret_cast<const V*>(o + row * D + part * Vec<T>::N);
-    const V b = *reinterpret_cast<const V*>(dout + row * D + part * Vec<T>::N);
-#pragma unroll
-    for (int i = 0; i < Vec<T>::N; ++i) s += to_f(a[i]) * to_f(b[i]);
-    if (dq_acc != nullptr) {
-      f32x4* z = reinterpret_cast<f32x4*>(dq_acc + row * D + part * Vec<T>::N);
-#pragma unroll
-      for (int i = 0; i < Vec<T>::N / 4; ++i) z[i] = f32x4{};
-    }
-  }
-  // reduce over the LPR lanes of the row (LPR is a power of two <= 32, aligned)
-#pragma unroll
-  for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if (live && part == 0) dvec[(int64_t)(row % hq) * total_q + row / hq] = s;
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void dq_finalize_kernel(const float* __restrict__ acc,
-                                                          T* __restrict__ dq, int64_t n4,
-                                                          const WsHeader* __restrict__ hdr) {
-  if (hdr != nullptr && hdr->status != BS_DEV_OK) return;  // planner rejected the input
+                                                          T* __restrict__ dq, int64_t n4) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
   const f32x4 x = reinterpret_cast<const f32x4*>(acc)[i];
@@ -166,38 +131,16 @@ hipError_t launch_lse_merge(const bs_dims& dims, const void* out_parts, const fl
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_preprocess(const bs_dims& dims, const void* out, const void* dout,
-                                 float* dvec, float* dq_acc_to_zero, const void* ws,
-                                 hipStream_t stream) {
-  const int64_t rows = dims.total_q * dims.hq;
-  if (rows == 0) return hipSuccess;
-  const int vec = dims.dtype == BS_BF16 ? 8 : 4;
-  const unsigned grid = blocks_for(rows * (dims.head_dim / vec));
-#define BS_PRE(T, D)                                                                          \
-  hipLaunchKernelGGL((preprocess_kernel<T, D>), dim3(grid), dim3(256), 0, stream,            \
-                     static_cast<const T*>(out), static_cast<const T*>(dout), rows, dims.hq,  \
-                     dims.total_q, dvec, dq_acc_to_zero,             \
-                     static_cast<const WsHeader*>(ws))
-  if (dims.dtype == BS_BF16) {
-    if (dims.head_dim == 128) BS_PRE(bf16, 128); else BS_PRE(bf16, 64);
-  } else {
-    if (dims.head_dim == 128) BS_PRE(float, 128); else BS_PRE(float, 64);
-  }
-#undef BS_PRE
-  return hipGetLastError();
-}
-
 hipError_t launch_dq_finalize(const bs_dims& dims, const float* dq_acc, void* dq,
-                              const void* ws, hipStream_t stream) {
-  const WsHeader* hdr = static_cast<const WsHeader*>(ws);
+                              hipStream_t stream) {
   const int64_t n4 = dims.total_q * dims.hq * dims.head_dim / 4;
   if (n4 == 0) return hipSuccess;
   if (dims.dtype == BS_BF16)
     hipLaunchKernelGGL(dq_finalize_kernel<bf16>, dim3(blocks_for(n4)), dim3(256), 0, stream,
-                       dq_acc, static_cast<bf16*>(dq), n4, hdr);
+                       dq_acc, static_cast<bf16*>(dq), n4);
   else
     hipLaunchKernelGGL(dq_finalize_kernel<float>, dim3(blocks_for(n4)), dim3(256), 0, stream,
-                       dq_acc, static_cast<float*>(dq), n4, hdr);
+                       dq_acc, static_cast<float*>(dq), n4);
   return hipGetLastError();
 }
 
