@@ -125,13 +125,15 @@ int bs_attn_varlen_fwd(const bs_dims* dims, const void* q, const void* k, const 
 
 /* Bytes of the per-device scratch array behind bs_attn_varlen_fwd_noalloc(). */
 #define BS_NOALLOC_SCRATCH_BYTES ((size_t)4 << 20)
+/* ... and of what follows it there: the partial results of calls of few queries per segment. */
+#define BS_NOALLOC_PIECE_BYTES ((size_t)16 << 20)
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): bs_attn_varlen_fwd without the
  * workspace arguments.  Same computation, arguments, layouts and results as
  * bs_attn_varlen_fwd; the plan that the forward kernel walks goes into a file-scope
- * device array of BS_NOALLOC_SCRATCH_BYTES (4 MiB) that the library holds on every
- * device it runs on until the process ends.  No hipMalloc or hipFree, and no allocating
+ * device array of BS_NOALLOC_SCRATCH_BYTES (4 MiB), followed by BS_NOALLOC_PIECE_BYTES
+ * (16 MiB), that the library holds on every device it runs on until the process ends.  No hipMalloc or hipFree, and no allocating
  * library routine, is called.
  *   - Limit: the plan takes 256 B + 4 (2 num_seqs + 3) B (each part rounded up to 256 B)
  *     + 48 B per work item, with ceil(total_q / 128) + num_seqs items (bf16) or

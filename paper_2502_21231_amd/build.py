@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libbs_attn.so")
 
-SOURCES = ["plan.hip", "fwd_bf16.hip", "dq_bf16.hip", "dkdv_bf16.hip", "f32.hip", "rowwise.hip",
+SOURCES = ["plan.hip", "fwd_bf16.hip", "few_bf16.hip", "dq_bf16.hip", "dkdv_bf16.hip", "f32.hip", "rowwise.hip",
            "xent.hip", "capi.hip"]
 # per-source additions: the dQ kernel's loop schedules faster under the backend's max-ILP
 # strategy (the forward's and dK/dV's do not)

@@ -92,6 +92,7 @@ struct WsLayout {
   size_t seg_dst;     // int32[num_seqs]
   size_t sorted;      // WorkItem[max_items]
   size_t dvec;        // float[hq * T]      (backward: rowsum(dO * O))
+  size_t few;         // pieces of the few-query forward; the general path needs the bytes before
   size_t total;
   int64_t max_items;
 };
@@ -194,7 +195,7 @@ __device__ __forceinline__ int swz_tr_base(int lane);
 // waits for all LDS reads (lgkmcnt(0)) before every use, which defeats reading LDS
 // operands ahead.  Byte offsets (R rows x gstride x 2 + 4 KB) stay below 2^31 for
 // the head counts the C API accepts.
-template <int K, int PER, int D>
+template <int K, int PER, int D, int AUX>
 struct DmaRun {
   static __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, bf16* lds, int row0,
                                                int sub, int phys, int gstride, int last) {
@@ -203,17 +204,18 @@ struct DmaRun {
     const int r = row < last ? row : last;
     const int voff = (r * gstride + ((phys ^ swz_g<D>(row)) << 3)) * 2 + 4096 - K * 1024;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16,
-                                             voff, 0, K * 1024, 0);
-    DmaRun<K + 1, PER, D>::issue(rs, lds, row0, sub, phys, gstride, last);
+                                             voff, 0, K * 1024, AUX);
+    DmaRun<K + 1, PER, D, AUX>::issue(rs, lds, row0, sub, phys, gstride, last);
   }
 };
-template <int PER, int D>
-struct DmaRun<PER, PER, D> {
+template <int PER, int D, int AUX>
+struct DmaRun<PER, PER, D, AUX> {
   static __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t, bf16*, int, int, int, int,
                                                int) {}
 };
 
-template <int D, int R, int NWAVES>
+// AUX: cache policy bits of the instruction (2: non-temporal).
+template <int D, int R, int NWAVES, int AUX = 0>
 __device__ __forceinline__ void dma_tile(bf16* lds_tile, const bf16* src, int gstride, int last,
                                          int wave, int lane) {
   constexpr int CPR = D / 8, RPI = 64 / CPR, NI = R / RPI, PER = NI / NWAVES;
@@ -223,7 +225,7 @@ __device__ __forceinline__ void dma_tile(bf16* lds_tile, const bf16* src, int gs
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(reinterpret_cast<const char*>(src) - 4096), 0, 0x7fffffff, 0x00020000);
   const int u0 = wave * PER;  // first instruction (1 KB of LDS) of this wave's run
-  DmaRun<0, PER, D>::issue(rsrc, lds_tile + u0 * RPI * D, u0 * RPI, sub, phys, gstride, last);
+  DmaRun<0, PER, D, AUX>::issue(rsrc, lds_tile + u0 * RPI * D, u0 * RPI, sub, phys, gstride, last);
 }
 
 // Element offset, in a swizzled tile, of this lane's 8-byte piece of the transposing
@@ -277,6 +279,22 @@ hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, co
                            int causal, float scale, void* out, float* lse,
                            const FwdMerge* merge, const void* ws, const WsLayout& L,
                            hipStream_t stream);
+// The forward of segments of few queries (few_bf16.hip): no plan, buf of F.bytes, the header
+// only for the status word.  cu_q, cu_k of at most kFewMaxSegs segments.
+constexpr int kFewMaxSegs = 1024;
+constexpr int kFewSlabs = 32;  // pieces of a row at most
+struct FewLayout {
+  size_t part, stat;  // offsets in buf of the pieces' sums and statistics (counts come first)
+  size_t bytes;       // 0: the call does not take this path
+  int32_t slabs;      // pieces of a row at most; 1: no row has two
+  int32_t per_min;    // key blocks per workgroup at least
+  int32_t blocks;     // workgroups
+};
+constexpr int few_block_keys(int head_dim) { return head_dim == 128 ? 128 : 256; }
+hipError_t launch_few_fwd(const bs_dims& dims, const void* q, const void* k, const void* v,
+                          const int32_t* cu_q, const int32_t* cu_k, int32_t num_seqs,
+                          int32_t max_seqlen, int causal, float scale, void* out, float* lse,
+                          void* hdr, void* buf, const FewLayout& F, hipStream_t stream);
 // The bf16 dQ kernel also forms D = rowsum(dO * O) and stores it in dvec for the dK/dV
 // kernel.
 hipError_t launch_dq_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,

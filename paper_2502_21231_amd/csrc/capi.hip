@@ -12,11 +12,13 @@
 #include "attn.hpp"
 
 // Scratch of the allocation-free forward (bs_attn_varlen_fwd_noalloc): the plan that the
-// forward kernel walks (header, per-segment offsets, work list).  Each device holds its own
+// forward kernel walks (header, per-segment offsets, work list), then the pieces of the
+// few-query forward (kFewBytes).  Each device holds its own
 // copy from the time the library's code is loaded on it until the process ends.  Host code
 // never uses this name as an address: the device address comes from hipGetSymbolAddress.
 constexpr size_t kNoAllocScratchBytes = BS_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+constexpr size_t kFewBytes = BS_NOALLOC_PIECE_BYTES;
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kFewBytes];
 
 namespace bs {
 namespace {
@@ -177,7 +179,67 @@ int check_scale(float s) {
   return BS_OK;
 }
 
-WsLayout layout_of(int op, const bs_dims& d, int64_t nseg) {
+// Whether a varlen forward takes the few-query kernel, from the sizes alone, and its buffers.
+//
+// The rule compares two estimates in microseconds (segments taken as equally long), fitted to
+// both kernels at 1..64 segments of 1..512 queries over 300..16K keys, MHA and GQA:
+//   few-query: 4, +5 for the merge, 4 per row block that a workgroup starts on average, and the
+//     larger of the key bytes at 5.3 TB/s (a third of that again for each further row block
+//     that reads them) and 1.6 per 128 keys of a 32-row block, shared evenly by 512 workgroups
+//     unless the bound on a row's pieces leaves some of them idle;
+//   general:   5 for its plan, 8 per 512 workgroups (one for each 128-row tile of a head), and
+//     the larger of the key bytes at 3.9 TB/s and 0.84 per 128 keys of a workgroup, 256 at a
+//     time, the longest segment's in a row; 13 at least.
+// Measured on both sides, us (few / general; segments x queries, longest segment, heads):
+//   32x1 8K 64/8: 76 / 336    16x16 4K 64/8: 61 / 100    16x8 4K 32/32: 79 / 110
+//   4x32 4K 64/8: 27 / 31     4x64 4K 64/8: 39 / 32      1x256 8K 64/8: 65 / 55
+//   2x128 8K 32/32: 30 / 51   1x256 8K 8/8: 24 / 54      30x55 1.4K 16/16: 64 / 55
+// and calls whose queries x heads leave room for fewer than two pieces per row (16 MiB, over
+// about 16K rows) stay on the general path.
+bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F) {
+  const double rows = (double)d.total_q * (d.hq / d.hkv), keys = (double)d.total_k / nseq / 128 + 1;
+  const double rb = rows / 32 + nseq / 2 > nseq ? rows / 32 + nseq / 2 : nseq;
+  const double mb = (double)d.total_k * d.hkv * d.head_dim * 4e-6;
+  const double per_wg = rb * d.hkv / 512, blocks = per_wg * keys * 128 / few_block_keys(d.head_dim);
+  const double few_c = 1.6 * keys * per_wg, few_m = mb / 5.3 * (1 + 0.35 * (rb / nseq - 1));
+  const double few = 4 + (F.slabs > 1 ? 5 : 0) + 4 * per_wg +
+                     (few_c > few_m ? few_c : few_m) * (F.per_min > blocks && blocks > 1 ? F.per_min / blocks : 1);
+  const double wgs = ((double)d.total_q / 128 + nseq) * d.hq / 256, row = longest / 128.0;
+  const double gen_c = 0.84 * (wgs * keys > row ? wgs * keys : row), gen_m = mb / 3.9;
+  const double gen = 5 + 4 * wgs + (gen_c > gen_m ? gen_c : gen_m);
+  return few < (gen > 13 ? gen : 13);
+}
+
+FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen) {
+  FewLayout F = {};
+  if (op != BS_OP_VARLEN_FWD || d.dtype != BS_BF16 || nseq < 1 || nseq > kFewMaxSegs) return F;
+  if (d.total_q < 1 || d.total_k < 1) return F;
+  const int64_t group = d.hq / d.hkv, rows = d.total_q * d.hq, blk = few_block_keys(d.head_dim);
+  // the line of key blocks: row blocks x key blocks of every segment, 32-bit per KV head
+  const int64_t line = (d.total_q * group / 32 + nseq) * (d.total_k / blk + nseq);
+  if (line >= (int64_t(1) << 31)) return F;
+  const int64_t longest = max_seqlen < d.total_k ? max_seqlen : d.total_k;
+  const int64_t nkb = (longest + blk - 1) / blk;  // key blocks of a segment at most
+  if (nkb <= 1) {
+    F.slabs = F.per_min = 1;
+    F.bytes = 256;
+  } else {  // a row's pieces: at most ceil(nkb / per) + 1
+    const size_t row_bytes = (size_t)(d.head_dim + 2) * sizeof(float);
+    F.stat = align256(sizeof(int32_t) * (size_t)rows);
+    if (F.stat + 512 + 2 * (size_t)rows * row_bytes > kFewBytes) return FewLayout{};
+    const size_t fit = (kFewBytes - F.stat - 512) / ((size_t)rows * row_bytes);
+    F.slabs = fit < kFewSlabs ? (int32_t)fit : kFewSlabs;
+    F.per_min = (int32_t)((nkb + F.slabs - 2) / (F.slabs - 1));
+    F.part = F.stat + align256(sizeof(float) * 2 * (size_t)(rows * F.slabs));
+    F.bytes = F.part + align256(sizeof(float) * (size_t)(rows * F.slabs * d.head_dim));
+  }
+  if (!few_pays(d, nseq, longest, F)) return FewLayout{};
+  const int64_t wgs = line * d.hkv;
+  F.blocks = wgs < 512 ? (int32_t)wgs : 512;  // two per CU
+  return F;
+}
+
+WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   WsLayout L = {};
   PlanCfg cfg[2];
   const int np = plans_of(op, d, cfg);
@@ -202,7 +264,8 @@ WsLayout layout_of(int op, const bs_dims& d, int64_t nseg) {
     if (writes_dq(op) && d.dtype == BS_F32)
       off += align256(sizeof(float) * (size_t)(d.total_q * d.hq * d.head_dim));
   }
-  L.total = off;
+  L.few = off;
+  L.total = off + few_layout(op, d, nseg, max_seqlen).bytes;
   L.max_items = mi;
   return L;
 }
@@ -211,7 +274,7 @@ int check_ws(const WsLayout& L, const void* ws, size_t bytes) {
   if (ws == nullptr) return fail(BS_ERR_WORKSPACE, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
     return fail(BS_ERR_WORKSPACE, "workspace is not 256-byte aligned");
-  if (bytes < L.total)
+  if (bytes < L.few)  // the general path's; without the rest the few-query forward is not taken
     return fail(BS_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", bytes,
                 L.total);
   return BS_OK;
@@ -264,12 +327,13 @@ bool overlaps(const void* a, int64_t na, const void* b, int64_t nb) {
 }
 
 // merge == NULL: writes the step's (out, lse).  Otherwise folds the step into the
-// running (merge->o_run, merge->lse_run); out is then optional (the final output).
+// running (merge->o_run, merge->lse_run); out is then optional (the final output).  pieces:
+// kFewBytes for the few-query forward, or NULL: what the workspace holds beyond the plan.
 int fwd_common(int op, const bs_dims* dims, const void* q, const void* k, const void* v,
                const int32_t* cu_q, const int32_t* cu_k, const int64_t* q_pos,
                const int64_t* k_pos, int32_t num_seqs, int32_t max_seqlen, int64_t q_off,
                int64_t k_off, int causal, float scale, void* out, float* lse,
-               const FwdMerge* merge, void* ws, size_t ws_bytes, void* stream) {
+               const FwdMerge* merge, void* ws, size_t ws_bytes, void* pieces, void* stream) {
   BS_TRY(check_dims(dims, true));
   const bs_dims& d = *dims;
   const int64_t qn = d.total_q * d.hq * d.head_dim, kn = d.total_k * d.hkv * d.head_dim;
@@ -290,9 +354,17 @@ int fwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   }
   BS_TRY(check_scale(scale));
   if (is_varlen(op)) BS_TRY(check_varlen_args(op, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen));
-  const WsLayout L = layout_of(op, d, is_varlen(op) ? num_seqs : 1);
+  const WsLayout L = layout_of(op, d, is_varlen(op) ? num_seqs : 1, max_seqlen);
   BS_TRY(check_ws(L, ws, ws_bytes));
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const FewLayout F = few_layout(op, d, num_seqs, max_seqlen);
+  if (F.bytes != 0 && (pieces != nullptr || ws_bytes >= L.total)) {
+    ProfScope ps(BS_KERNEL_FWD, s);
+    BS_HIP(launch_few_fwd(d, q, k, v, cu_q, cu_k, num_seqs, max_seqlen, causal, scale, out, lse, ws,
+                          pieces != nullptr ? pieces : static_cast<char*>(ws) + L.few, F, s),
+           "few-query forward launch");
+    return ok();
+  }
   WsLayout Lp;
   {
     ProfScope ps(BS_KERNEL_PLAN, s);
@@ -332,7 +404,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   else BS_TRY(check_ptr(dq_accum, qn, "dq_accum"));
   BS_TRY(check_scale(scale));
   if (varlen) BS_TRY(check_varlen_args(op, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen));
-  const WsLayout L = layout_of(op, d, varlen ? num_seqs : 1);
+  const WsLayout L = layout_of(op, d, varlen ? num_seqs : 1, max_seqlen);
   BS_TRY(check_ws(L, ws, ws_bytes));
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* base = static_cast<char*>(ws);
@@ -424,7 +496,7 @@ size_t bs_attn_workspace_size(int op, const bs_dims* dims, int32_t num_seqs, int
     return 0;
   }
   ok();
-  return layout_of(op, *dims, is_varlen(op) ? num_seqs : 1).total;
+  return layout_of(op, *dims, is_varlen(op) ? num_seqs : 1, max_seqlen).total;
 }
 
 int bs_attn_varlen_fwd(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -433,7 +505,7 @@ int bs_attn_varlen_fwd(const bs_dims* dims, const void* q, const void* k, const 
                        void* workspace, size_t workspace_bytes, void* stream) {
   return fwd_common(BS_OP_VARLEN_FWD, dims, q, k, v, cu_seqlens_q, cu_seqlens_k, nullptr, nullptr,
                     num_seqs, max_seqlen, 0, 0, causal, scale, out, lse, nullptr, workspace,
-                    workspace_bytes, stream);
+                    workspace_bytes, nullptr, stream);
 }
 
 int bs_attn_varlen_fwd_noalloc(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -443,7 +515,7 @@ int bs_attn_varlen_fwd_noalloc(const bs_dims* dims, const void* q, const void* k
   BS_TRY(check_dims(dims, true));
   BS_TRY(check_varlen_args(BS_OP_VARLEN_FWD, cu_seqlens_q, cu_seqlens_k, nullptr, nullptr,
                            num_seqs, max_seqlen));
-  const size_t need = layout_of(BS_OP_VARLEN_FWD, *dims, num_seqs).total;
+  const size_t need = layout_of(BS_OP_VARLEN_FWD, *dims, num_seqs, max_seqlen).few;
   if (need > kNoAllocScratchBytes)
     return fail(BS_ERR_WORKSPACE,
                 "these sizes need %zu bytes of plan scratch, more than the %zu bytes of the "
@@ -453,7 +525,7 @@ int bs_attn_varlen_fwd_noalloc(const bs_dims* dims, const void* q, const void* k
   BS_TRY(noalloc_scratch(stream, &ws));
   return fwd_common(BS_OP_VARLEN_FWD, dims, q, k, v, cu_seqlens_q, cu_seqlens_k, nullptr, nullptr,
                     num_seqs, max_seqlen, 0, 0, causal, scale, out, lse, nullptr, ws,
-                    kNoAllocScratchBytes, stream);
+                    kNoAllocScratchBytes, static_cast<char*>(ws) + kNoAllocScratchBytes, stream);
 }
 
 int bs_attn_varlen_bwd(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -472,7 +544,7 @@ int bs_attn_chunk_fwd(const bs_dims* dims, const void* q, const void* k, const v
                       void* stream) {
   return fwd_common(BS_OP_CHUNK_FWD, dims, q, k, v, nullptr, nullptr, nullptr, nullptr, 1, 0,
                     q_pos_offset, k_pos_offset, causal, scale, out, lse, nullptr, workspace,
-                    workspace_bytes, stream);
+                    workspace_bytes, nullptr, stream);
 }
 
 int bs_attn_chunk_fwd_merge(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -482,7 +554,7 @@ int bs_attn_chunk_fwd_merge(const bs_dims* dims, const void* q, const void* k, c
   const FwdMerge m{o_run, lse_run, accumulate != 0};
   return fwd_common(BS_OP_CHUNK_FWD, dims, q, k, v, nullptr, nullptr, nullptr, nullptr, 1, 0,
                     q_pos_offset, k_pos_offset, causal, scale, out, nullptr, &m, workspace,
-                    workspace_bytes, stream);
+                    workspace_bytes, nullptr, stream);
 }
 
 int bs_attn_chunk_bwd(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -502,7 +574,7 @@ int bs_attn_packed_chunk_fwd(const bs_dims* dims, const void* q, const void* k, 
                              void* workspace, size_t workspace_bytes, void* stream) {
   return fwd_common(BS_OP_PACKED_CHUNK_FWD, dims, q, k, v, cu_seqlens_q, cu_seqlens_k, q_pos,
                     k_pos, num_seqs, max_seqlen, 0, 0, causal, scale, out, lse, nullptr,
-                    workspace, workspace_bytes, stream);
+                    workspace, workspace_bytes, nullptr, stream);
 }
 
 int bs_attn_packed_chunk_fwd_merge(const bs_dims* dims, const void* q, const void* k,
@@ -515,7 +587,7 @@ int bs_attn_packed_chunk_fwd_merge(const bs_dims* dims, const void* q, const voi
   const FwdMerge m{o_run, lse_run, accumulate != 0};
   return fwd_common(BS_OP_PACKED_CHUNK_FWD, dims, q, k, v, cu_seqlens_q, cu_seqlens_k, q_pos,
                     k_pos, num_seqs, max_seqlen, 0, 0, causal, scale, out, nullptr, &m,
-                    workspace, workspace_bytes, stream);
+                    workspace, workspace_bytes, nullptr, stream);
 }
 
 int bs_attn_packed_chunk_bwd(const bs_dims* dims, const void* q, const void* k, const void* v,
@@ -625,7 +697,7 @@ int bs_attn_plan_export(int op, const bs_dims* dims, const int32_t* cu_seqlens_q
   const bool varlen = is_varlen(op);
   if (varlen)
     BS_TRY(check_varlen_args(op, cu_seqlens_q, cu_seqlens_k, q_pos, k_pos, num_seqs, max_seqlen));
-  const WsLayout L = layout_of(op, *dims, varlen ? num_seqs : 1);
+  const WsLayout L = layout_of(op, *dims, varlen ? num_seqs : 1, max_seqlen);
   BS_TRY(check_ws(L, workspace, workspace_bytes));
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the plan the op's main kernel walks: the last one of the op
