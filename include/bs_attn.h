@@ -105,7 +105,9 @@ enum {
 };
 
 /* Bytes of workspace that `op` needs for these sizes (num_seqs, max_seqlen are
- * ignored by the two single-chunk ops).  Returns 0 when the arguments are invalid (then
+ * ignored by the two single-chunk ops).  Calls of few workgroups ask for room for partial
+ * results too (16 MiB at most forward, 64 MiB backward); with a workspace that holds the plan
+ * (and, backward, D) but not that room they run without it, slower.  Returns 0 when the arguments are invalid (then
  * bs_last_error() says why).  The workspace needs no initialisation and holds
  * nothing across calls except what bs_read_device_status() reads. */
 size_t bs_attn_workspace_size(int op, const bs_dims* dims, int32_t num_seqs, int32_t max_seqlen);

@@ -87,12 +87,181 @@ __device__ __forceinline__ bool block_work(int b, const WsHeader* __restrict__ h
   return true;
 }
 
+// Segment b of the problem: query start/length, key start/length, diagonal.
+struct Seg {
+  int64_t q0, lq, k0, lk;
+  int32_t diag;
+};
+
+__device__ __forceinline__ int32_t clamp_diag(int64_t d) {
+  return (int32_t)(d < -kDiagClamp ? -kDiagClamp : (d > kDiagClamp ? kDiagClamp : d));
+}
+
+// Diagonal: key j visible to query i iff j - i <= diag.  Varlen segments are
+// aligned bottom-right (diag = len_k - len_q); packed chunk segments and single
+// chunks take it from the global positions of their first query and key.
+__device__ __forceinline__ Seg load_seg(const int32_t* cu_q, const int32_t* cu_k,
+                                        const int64_t* q_pos, const int64_t* k_pos, int32_t b,
+                                        int64_t total_q, int64_t total_k, int32_t diag_chunk) {
+  Seg s;
+  if (cu_q == nullptr) {  // chunk mode: one segment, diagonal from the offsets
+    s.q0 = 0; s.lq = total_q; s.k0 = 0; s.lk = total_k; s.diag = diag_chunk;
+  } else {
+    s.q0 = cu_q[b]; s.lq = (int64_t)cu_q[b + 1] - cu_q[b];
+    s.k0 = cu_k[b]; s.lk = (int64_t)cu_k[b + 1] - cu_k[b];
+    s.diag = q_pos == nullptr ? clamp_diag(s.lk - s.lq) : clamp_diag(q_pos[b] - k_pos[b]);
+  }
+  return s;
+}
+
+// Work item `tile` of segment b (run0, nrun: its segment's run in the list).
+__device__ __forceinline__ WorkItem make_item(const Seg& s, int32_t b, int64_t tile, int causal,
+                                              int kind, int tile_a, int tile_b, int32_t run0,
+                                              int32_t nrun) {
+  const int64_t diag = s.diag;
+  WorkItem w;
+  w.seg = b; w.tile = (int32_t)tile; w.diag = s.diag; w.run0 = run0; w.nrun = nrun;
+  if (kind == kPlanFwd) {
+    const int64_t BM = tile_a, BN = tile_b;
+    const int64_t q_first = tile * BM;
+    const int64_t q_last = (q_first + BM < s.lq ? q_first + BM : s.lq) - 1;
+    const int64_t nkt = (s.lk + BN - 1) / BN;
+    int64_t n_tiles, n_full;
+    if (causal) {
+      const int64_t lim = q_last + diag;
+      n_tiles = lim < 0 ? 0 : (lim / BN + 1 < nkt ? lim / BN + 1 : nkt);
+      int64_t f = q_first + diag + 1;
+      f = f < s.lk ? f : s.lk;
+      n_full = f > 0 ? f / BN : 0;
+    } else {
+      n_tiles = nkt;
+      n_full = s.lk / BN;
+    }
+    w.a_start = (int32_t)(s.q0 + q_first);
+    w.a_rows = (int32_t)(q_last - q_first + 1);
+    w.b_start = (int32_t)s.k0;
+    w.b_len = (int32_t)s.lk;
+    w.n0 = (int32_t)n_full;
+    w.n1 = (int32_t)n_tiles;
+    w.n2 = (int32_t)n_tiles;
+  } else {
+    const int64_t BM = tile_b, BN = tile_a;
+    const int64_t k_first = tile * BN;
+    const int64_t nqt = (s.lq + BM - 1) / BM;
+    const bool in_range = k_first + BN <= s.lk;
+    int64_t first, ffirst;
+    if (causal) {
+      const int64_t r = k_first - diag;  // first query row that sees key k_first
+      first = r > s.lq - 1 ? nqt : (r > 0 ? r / BM : 0);
+      if (!in_range) {
+        ffirst = nqt;
+      } else {
+        const int64_t t = k_first + BN - 1 - diag;  // FULL needs q_first >= t
+        ffirst = t <= 0 ? 0 : (t + BM - 1) / BM;
+        ffirst = ffirst < nqt ? ffirst : nqt;
+      }
+    } else {
+      first = 0;
+      ffirst = in_range ? 0 : nqt;
+    }
+    const int64_t n_vis = nqt - first;
+    const int64_t n_masked = ffirst - first > 0 ? ffirst - first : 0;
+    w.a_start = (int32_t)(s.k0 + k_first);
+    w.a_rows = (int32_t)(s.lk - k_first < BN ? s.lk - k_first : BN);
+    w.b_start = (int32_t)s.q0;
+    w.b_len = (int32_t)s.lq;
+    w.n0 = (int32_t)first;
+    w.n1 = (int32_t)n_masked;
+    w.n2 = (int32_t)n_vis;
+  }
+  return w;
+}
+
+// What a kernel needs to find its own work item (no planning launch), for grids that the chip
+// holds at once: the order of the list does not matter then, and a workgroup reads cu_seqlens
+// about as fast as a work item.
+constexpr int kSelfMaxSegs = 256;
+struct PlanArgs {
+  const int32_t* cu_q;  // NULL: one chunk with diagonal diag_chunk
+  const int32_t* cu_k;
+  const int64_t* q_pos;
+  const int64_t* k_pos;
+  WsHeader* hdr;
+  int64_t total_q, total_k;
+  int32_t num_seqs, max_seqlen, diag_chunk;
+};
+
+// Item i of the unordered list (segments in order, tiles ascending) for a workgroup of at least
+// kSelfMaxSegs threads; false when there is none or cu_seqlens is rejected.  Block 0 writes the
+// header.  lds: kSelfMaxSegs + 8 int32.
+__device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kind, int tile_a,
+                                          int tile_b, int32_t i, int32_t* lds, WorkItem& it) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (a.cu_q == nullptr) {
+    const Seg s = load_seg(nullptr, nullptr, nullptr, nullptr, 0, a.total_q, a.total_k, a.diag_chunk);
+    const int32_t n = (int32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a);
+    if (blockIdx.x == 0 && tid == 0) {
+      a.hdr->status = BS_DEV_OK;
+      a.hdr->n_items = n;
+    }
+    if (i >= n) return false;
+    it = make_item(s, 0, i, causal, kind, tile_a, tile_b, 0, n);
+    return true;
+  }
+  int32_t* pre = lds;                     // items before each segment
+  int32_t* wsum = lds + kSelfMaxSegs + 1; // of each of the first four waves
+  int32_t* bad = wsum + 4;
+  if (tid == 0) *bad = BS_DEV_OK;
+  __syncthreads();
+  int32_t cnt = 0;
+  if (tid < a.num_seqs) {
+    const Seg s = load_seg(a.cu_q, a.cu_k, nullptr, nullptr, tid, a.total_q, a.total_k, 0);
+    if (s.lq < 0 || s.lk < 0) atomicCAS(bad, 0, BS_DEV_NOT_MONOTONE);
+    else if (s.lq > a.max_seqlen || s.lk > a.max_seqlen) atomicCAS(bad, 0, BS_DEV_TOO_LONG);
+    else cnt = (int32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a);
+  }
+  if (tid == 0) {
+    if (a.cu_q[0] != 0 || a.cu_k[0] != 0) atomicExch(bad, BS_DEV_BAD_FIRST);
+    else if (a.cu_q[a.num_seqs] != a.total_q || a.cu_k[a.num_seqs] != a.total_k)
+      atomicExch(bad, BS_DEV_BAD_TOTAL);
+  }
+  int32_t run = cnt;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t x = __shfl_up(run, off);
+    if (lane >= off) run += x;
+  }
+  if (tid < kSelfMaxSegs && lane == 63) wsum[tid >> 6] = run;
+  __syncthreads();
+  if (tid < kSelfMaxSegs) {
+    int32_t at = run - cnt;
+    for (int w = 0; w < (tid >> 6); ++w) at += wsum[w];
+    if (tid <= a.num_seqs) pre[tid] = at;
+    if (tid == kSelfMaxSegs - 1 && a.num_seqs == kSelfMaxSegs) pre[kSelfMaxSegs] = at + cnt;
+  }
+  __syncthreads();
+  const int32_t code = *bad, n = pre[a.num_seqs];
+  if (blockIdx.x == 0 && tid == 0) {
+    a.hdr->status = code;
+    a.hdr->n_items = code == BS_DEV_OK ? n : 0;
+  }
+  if (code != BS_DEV_OK || i >= n) return false;  // uniform
+  int32_t lo = 0, hi = a.num_seqs - 1;
+  while (lo < hi) {  // the last segment whose items begin at or before i (empty ones skipped)
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (pre[mid] <= i) lo = mid; else hi = mid - 1;
+  }
+  const Seg s = load_seg(a.cu_q, a.cu_k, a.q_pos, a.k_pos, lo, a.total_q, a.total_k, 0);
+  it = make_item(s, lo, i - pre[lo], causal, kind, tile_a, tile_b, pre[lo], pre[lo + 1] - pre[lo]);
+  return true;
+}
+
 struct WsLayout {
   size_t seg_off;     // int32[num_seqs + 1]
   size_t seg_dst;     // int32[num_seqs]
   size_t sorted;      // WorkItem[max_items]
   size_t dvec;        // float[hq * T]      (backward: rowsum(dO * O))
-  size_t few;         // pieces of the few-query forward; the general path needs the bytes before
+  size_t extra;       // pieces of the few-query forward, or partials of split chains: optional
   size_t total;
   int64_t max_items;
 };
@@ -274,11 +443,30 @@ struct FwdMerge {
   int accumulate;
 };
 
-// merge == NULL: plain forward writing (out, lse)
+// A grid that the chip holds at once: its workgroups plan for themselves (plan.hdr set), and
+// `splits` of them share each work item's chain of tiles.  With splits > 1 every one leaves a
+// float32 partial in `part` (slab s of splits; [rows][d] in the layout of the output, twice for
+// dK and dV; the forward's followed by float2 (max in log2 units, sum) [splits][T * hq]) and a
+// second kernel combines them.
+struct SelfPlan {
+  PlanArgs plan;
+  int64_t items;  // work items at most
+  int32_t splits;
+  float* part;
+};
+
+// merge == NULL: plain forward writing (out, lse).  self == NULL: the work list in ws.
 hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                            int causal, float scale, void* out, float* lse,
                            const FwdMerge* merge, const void* ws, const WsLayout& L,
-                           hipStream_t stream);
+                           const SelfPlan* self, hipStream_t stream);
+// Combines the forward's partials into (out, lse) or the running state.
+hipError_t launch_fwd_combine(const bs_dims& dims, const SelfPlan& self, void* out, float* lse,
+                              const FwdMerge* merge, hipStream_t stream);
+// out0 / out1 (one of them may be NULL) = sum of the slabs of n floats, slab s of out0 at part +
+// s n, of out1 behind out0's: written as bf16, or added into float32.
+hipError_t launch_sum_slabs(const float* part, int splits, int64_t n, void* out0, void* out1,
+                            int accumulate_f32, const WsHeader* hdr, hipStream_t stream);
 // The forward of segments of few queries (few_bf16.hip): no plan, buf of F.bytes, the header
 // only for the status word.  cu_q, cu_k of at most kFewMaxSegs segments.
 constexpr int kFewMaxSegs = 1024;
@@ -300,11 +488,11 @@ hipError_t launch_few_fwd(const bs_dims& dims, const void* q, const void* k, con
 hipError_t launch_dq_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                           const void* out, const void* dout, const float* lse, float* dvec,
                           int causal, float scale, void* dq, float* dq_acc, const void* ws,
-                          const WsLayout& L, hipStream_t stream);
+                          const WsLayout& L, const SelfPlan* self, hipStream_t stream);
 hipError_t launch_dkdv_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                             const void* dout, const float* lse, const float* dvec, int causal,
                             float scale, void* dk, void* dv, int kv_accumulate, const void* ws,
-                            const WsLayout& L, hipStream_t stream);
+                            const WsLayout& L, const SelfPlan* self, hipStream_t stream);
 
 hipError_t launch_fwd_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
                           int causal, float scale, void* out, float* lse, const FwdMerge* merge,

@@ -28,6 +28,7 @@ struct BwdParams {
   int32_t hq, hkv, group;
   int32_t causal;
   float scale, scale_log2;
+  SelfPlan self;     // kSelf
 };
 
 inline BwdParams make_params(const bs_dims& dims, const void* q, const void* k, const void* v,

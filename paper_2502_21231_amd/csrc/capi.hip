@@ -239,6 +239,74 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
   return F;
 }
 
+// How a bf16 kernel of few workgroups runs: by its own plan (no list), each work item's chain of
+// tiles split over `splits` workgroups.
+struct SelfCfg {
+  bool self;
+  int32_t splits;
+  int64_t items;
+  size_t bytes;  // of the partials (0: none)
+};
+enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
+
+// The rule, from the sizes: at most as many workgroups as the chip holds at once (two per CU for
+// the forward and dQ, one for dK/dV: then the list's order does not matter), and the number of
+// parts (at most 8) with the smallest estimate in microseconds
+//   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
+//   partials' bytes, written and read, at 3 TB/s,
+// t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one),
+// the measured times of a chain on a CU.  Forward + backward, us, by the list / by this rule:
+//   512 tokens, 8/8 heads: 62 / 53 (no chain split: the three planning launches)
+//   507 tokens, 40/8: 96 / 62    854 tokens, 32/4: 140 / 76    688 tokens, 64/8: 134 / 80
+// and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
+// subsequences, 16/2 heads: 538 / 346.  Partials: 16 MiB at most in the forward (what the
+// allocation-free entry point holds), 64 MiB in the backward.
+SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
+  SelfCfg c = {false, 1, 0, 0};
+  const bool varlen = is_varlen(op);
+  if (d.dtype != BS_BF16 || (varlen && (nseg < 1 || nseg > kSelfMaxSegs))) return c;
+  PlanCfg cfg[2];
+  plans_of(op, d, cfg);
+  const bool dkdv = k == kSelfDkdv;
+  const int64_t slots = dkdv ? 256 : 512;
+  c.items = max_items_of(cfg[dkdv ? 1 : 0], d, nseg, varlen);
+  const int64_t wgs = c.items * (dkdv ? d.hkv : d.hq);
+  if (wgs < 1 || wgs > slots) return c;
+  c.self = true;
+  const int64_t len = dkdv ? d.total_q : d.total_k;
+  const int64_t longest = varlen && max_seqlen < len ? max_seqlen : len;
+  const int64_t bm = bwd_bm(d.head_dim);
+  const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
+  const double t = dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
+  const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
+  const size_t slab = rows * (d.head_dim + (k == kSelfFwd ? 2 : 0)) * sizeof(float);
+  const size_t limit = k == kSelfFwd ? kFewBytes : (size_t)64 << 20;
+  double best = 0;
+  for (int32_t s = 1; s <= 8 && s <= chain && (s == 1 || s * slab <= limit); ++s) {
+    const double cost = (double)((wgs * s + slots - 1) / slots) * chain / s * t +
+                        (s > 1 ? 5 + 2e-6 * (double)(s * slab) / 3 : 0);
+    if (s == 1 || cost < best) {
+      best = cost;
+      c.splits = s;
+    }
+  }
+  c.bytes = c.splits > 1 ? align256(c.splits * slab) : 0;
+  return c;
+}
+
+// Room beyond the plan and D.  The backward's is the same for both dtypes, so that a float32
+// call's workspace also holds the bf16 call of its sizes.
+size_t extra_bytes(int op, bs_dims d, int64_t nseg, int64_t max_seqlen) {
+  if (is_bwd(op)) d.dtype = BS_BF16;
+  if (!is_bwd(op)) {
+    const size_t a = few_layout(op, d, nseg, max_seqlen).bytes;
+    return a != 0 ? a : self_cfg(kSelfFwd, op, d, nseg, max_seqlen).bytes;
+  }
+  const size_t a = self_cfg(kSelfDq, op, d, nseg, max_seqlen).bytes;
+  const size_t b = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen).bytes;
+  return a > b ? a : b;
+}
+
 WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   WsLayout L = {};
   PlanCfg cfg[2];
@@ -264,8 +332,8 @@ WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
     if (writes_dq(op) && d.dtype == BS_F32)
       off += align256(sizeof(float) * (size_t)(d.total_q * d.hq * d.head_dim));
   }
-  L.few = off;
-  L.total = off + few_layout(op, d, nseg, max_seqlen).bytes;
+  L.extra = off;
+  L.total = off + extra_bytes(op, d, nseg, max_seqlen);
   L.max_items = mi;
   return L;
 }
@@ -274,7 +342,7 @@ int check_ws(const WsLayout& L, const void* ws, size_t bytes) {
   if (ws == nullptr) return fail(BS_ERR_WORKSPACE, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
     return fail(BS_ERR_WORKSPACE, "workspace is not 256-byte aligned");
-  if (bytes < L.few)  // the general path's; without the rest the few-query forward is not taken
+  if (bytes < L.extra)  // without the rest no chain is split, nor the few-query forward taken
     return fail(BS_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", bytes,
                 L.total);
   return BS_OK;
@@ -297,6 +365,32 @@ hipError_t run_plan(int op, const bs_dims& d, int i, const int32_t* cu_q, const 
                      packed ? q_pos : nullptr, packed ? k_pos : nullptr,
                      varlen ? num_seqs : 1, d.total_q, d.total_k, max_seqlen, (int32_t)diag,
                      causal, cfg[i].tile_a, cfg[i].tile_b, Lp->max_items, ws, *Lp, s);
+}
+
+// The self-planned form of a kernel for this call (NULL: by the list); buf: room for partials
+// or NULL.
+const SelfPlan* self_plan_of(SelfKernel k, int op, const bs_dims& d, const int32_t* cu_q,
+                             const int32_t* cu_k, const int64_t* q_pos, const int64_t* k_pos,
+                             int32_t num_seqs, int32_t max_seqlen, int64_t q_off, int64_t k_off,
+                             void* ws, void* buf, SelfPlan* sp) {
+  const SelfCfg c = self_cfg(k, op, d, is_varlen(op) ? num_seqs : 1, max_seqlen);
+  if (!c.self) return nullptr;
+  const int64_t diag = q_off - k_off;
+  PlanArgs& a = sp->plan;
+  a.cu_q = is_varlen(op) ? cu_q : nullptr;
+  a.cu_k = is_varlen(op) ? cu_k : nullptr;
+  a.q_pos = is_packed(op) ? q_pos : nullptr;
+  a.k_pos = is_packed(op) ? k_pos : nullptr;
+  a.hdr = static_cast<WsHeader*>(ws);
+  a.total_q = d.total_q;
+  a.total_k = d.total_k;
+  a.num_seqs = num_seqs;
+  a.max_seqlen = max_seqlen;
+  a.diag_chunk = (int32_t)(diag < -kDiagClamp ? -kDiagClamp : (diag > kDiagClamp ? kDiagClamp : diag));
+  sp->items = c.items;
+  sp->splits = buf != nullptr ? c.splits : 1;
+  sp->part = static_cast<float*>(buf);
+  return sp;
 }
 
 int check_varlen_args(int op, const int32_t* cu_q, const int32_t* cu_k, const int64_t* q_pos,
@@ -361,22 +455,28 @@ int fwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   if (F.bytes != 0 && (pieces != nullptr || ws_bytes >= L.total)) {
     ProfScope ps(BS_KERNEL_FWD, s);
     BS_HIP(launch_few_fwd(d, q, k, v, cu_q, cu_k, num_seqs, max_seqlen, causal, scale, out, lse, ws,
-                          pieces != nullptr ? pieces : static_cast<char*>(ws) + L.few, F, s),
+                          pieces != nullptr ? pieces : static_cast<char*>(ws) + L.extra, F, s),
            "few-query forward launch");
     return ok();
   }
-  WsLayout Lp;
-  {
+  WsLayout Lp = L;
+  SelfPlan sp;
+  void* buf = pieces != nullptr ? pieces : (ws_bytes >= L.total ? static_cast<char*>(ws) + L.extra : nullptr);
+  const SelfPlan* self = self_plan_of(kSelfFwd, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen,
+                                      q_off, k_off, ws, buf, &sp);
+  if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 0, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
                     causal, ws, L, &Lp, s),
            "planner launch");
   }
   ProfScope ps(BS_KERNEL_FWD, s);
-  if (d.dtype == BS_BF16)
-    BS_HIP(launch_fwd_bf16(d, q, k, v, causal, scale, out, lse, merge, ws, Lp, s),
+  if (d.dtype == BS_BF16) {
+    BS_HIP(launch_fwd_bf16(d, q, k, v, causal, scale, out, lse, merge, ws, Lp, self, s),
            "forward launch");
-  else
+    if (self != nullptr && self->splits > 1)
+      BS_HIP(launch_fwd_combine(d, *self, out, lse, merge, s), "forward combine launch");
+  } else
     BS_HIP(launch_fwd_f32(d, q, k, v, causal, scale, out, lse, merge, ws, Lp, s),
            "forward launch");
   return ok();
@@ -410,8 +510,13 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   char* base = static_cast<char*>(ws);
   float* dvec = reinterpret_cast<float*>(base + L.dvec);
   const bool f32 = d.dtype == BS_F32;
-  WsLayout Lp;
-  {
+  WsLayout Lp = L;
+  SelfPlan sp;
+  void* buf = ws_bytes >= L.total ? base + L.extra : nullptr;
+  const SelfPlan* self = self_plan_of(kSelfDq, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen,
+                                      q_off, k_off, ws, buf, &sp);
+  const WsHeader* hdr = static_cast<const WsHeader*>(ws);
+  if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 0, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
                     causal, ws, L, &Lp, s),
@@ -425,10 +530,17 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
              "backward dQ launch");
     else
       BS_HIP(launch_dq_bf16(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : nullptr,
-                            dq_accum, ws, Lp, s),
+                            dq_accum, ws, Lp, self, s),
              "backward dQ launch");
+    if (self != nullptr && self->splits > 1 && qn > 0)
+      BS_HIP(launch_sum_slabs(self->part, self->splits, qn, direct ? dq : dq_accum, nullptr, !direct,
+                              hdr, s),
+             "dQ sum launch");
   }
-  {
+  self = self_plan_of(kSelfDkdv, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
+                      ws, buf, &sp);
+  Lp = L;
+  if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 1, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
                     causal, ws, L, &Lp, s),
@@ -442,8 +554,11 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
              "backward dK/dV launch");
     else
       BS_HIP(launch_dkdv_bf16(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate,
-                              ws, Lp, s),
+                              ws, Lp, self, s),
              "backward dK/dV launch");
+    if (self != nullptr && self->splits > 1 && kn > 0)
+      BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv, kv_accumulate, hdr, s),
+             "dK/dV sum launch");
   }
   return ok();
 }
@@ -515,7 +630,7 @@ int bs_attn_varlen_fwd_noalloc(const bs_dims* dims, const void* q, const void* k
   BS_TRY(check_dims(dims, true));
   BS_TRY(check_varlen_args(BS_OP_VARLEN_FWD, cu_seqlens_q, cu_seqlens_k, nullptr, nullptr,
                            num_seqs, max_seqlen));
-  const size_t need = layout_of(BS_OP_VARLEN_FWD, *dims, num_seqs, max_seqlen).few;
+  const size_t need = layout_of(BS_OP_VARLEN_FWD, *dims, num_seqs, max_seqlen).extra;
   if (need > kNoAllocScratchBytes)
     return fail(BS_ERR_WORKSPACE,
                 "these sizes need %zu bytes of plan scratch, more than the %zu bytes of the "

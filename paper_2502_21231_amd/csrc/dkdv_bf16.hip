@@ -46,7 +46,7 @@
 namespace bs {
 namespace {
 
-template <int D, bool kGroupOrder>
+template <int D, bool kGroupOrder, bool kSelf>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dkdv_bf16_kernel(const BwdParams p) {
   constexpr int BM = bwd_bm(D), BN = kBwdBN;
@@ -69,7 +69,17 @@ void dkdv_bf16_kernel(const BwdParams p) {
 
   WorkItem it;
   int hk;  // KV head; each reads the Q/dO stream of its own query heads
-  if (!block_work(blockIdx.x, p.hdr, p.items, p.hkv, 1, kHeadMajorRowsDkdv, it, hk)) return;
+  int slab = 0;
+  if constexpr (kSelf) {
+    __shared__ int32_t pl[kSelfMaxSegs + 8];
+    const int b = blockIdx.x / p.hkv;
+    hk = blockIdx.x - b * p.hkv;
+    const int i = b / p.self.splits;
+    slab = b - i * p.self.splits;
+    if (!self_plan(p.self.plan, p.causal, kPlanBwd, BN, BM, i, pl, it)) return;
+  } else {
+    if (!block_work(blockIdx.x, p.hdr, p.items, p.hkv, 1, kHeadMajorRowsDkdv, it, hk)) return;
+  }
 
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, c = lane & 31, hh = lane >> 5;
@@ -99,7 +109,11 @@ void dkdv_bf16_kernel(const BwdParams p) {
   const int q_len = it.b_len;
   const int qt_first = it.n0, n_masked = it.n1, n_vis = it.n2;
   const int diag = it.diag;
-  const int n_iter = n_vis * p.group;
+  int i_first = 0, n_iter = n_vis * p.group;  // this workgroup's steps: i_first .. n_iter - 1
+  if constexpr (kSelf) {
+    i_first = slab * n_iter / p.self.splits;
+    n_iter = (slab + 1) * n_iter / p.self.splits;
+  }
   // step i: query tile j (relative to qt_first) of query head hg of the group
   auto tile_of = [&](int i, int& hg, int& j) {
     if constexpr (kGroupOrder) {  // last tile first, heads innermost
@@ -144,9 +158,9 @@ void dkdv_bf16_kernel(const BwdParams p) {
       Rd[ct] = row_ok ? row_r : 0.f;
   };
 
-  if (n_iter > 0) copy_tile(0, QD0);
-  wait_vmem_all();  // K / V row, tile 0 and its rows
-  if (role == 0 && n_iter > 0) store_rows(R0);
+  if (n_iter > i_first) copy_tile(i_first, QD0);
+  wait_vmem_all();  // K / V row, the first tile and its rows
+  if (role == 0 && n_iter > i_first) store_rows(R0);
   __syncthreads();
 
   // phase 1 reads rows of Q (role 0) or dO (role 1); phase 2 reads dO (role 0)
@@ -272,7 +286,7 @@ void dkdv_bf16_kernel(const BwdParams p) {
     if (role == 0 && i + 1 < n_iter) store_rows(Rn);
     __syncthreads();
   };
-  for (int i = 0; i < n_iter; i += 2) {
+  for (int i = i_first; i < n_iter; i += 2) {
     step(i, QD0, R0, QD1, R1);
     if (i + 1 < n_iter) step(i + 1, QD1, R1, QD0, R0);
   }
@@ -290,6 +304,13 @@ void dkdv_bf16_kernel(const BwdParams p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) g[e] = acc[db][a * 4 + e] * mul;
         const int col = db * 32 + a * 8;
+        if constexpr (kSelf) {
+          if (p.self.splits > 1) {  // dV's slabs come behind dK's
+            const int64_t n = p.self.plan.total_k * kvstride;
+            *reinterpret_cast<f32x4*>(p.self.part + ((1 - role) * p.self.splits + slab) * n + off + col) = g;
+            continue;
+          }
+        }
         if (gacc != nullptr) {  // add into float32 accumulators
           f32x4* dst = reinterpret_cast<f32x4*>(gacc + off + col);
           *dst = *dst + g;
@@ -308,7 +329,7 @@ void dkdv_bf16_kernel(const BwdParams p) {
 hipError_t launch_dkdv_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                             const void* dout, const float* lse, const float* dvec, int causal,
                             float scale, void* dk, void* dv, int kv_accumulate, const void* ws,
-                            const WsLayout& L, hipStream_t stream) {
+                            const WsLayout& L, const SelfPlan* self, hipStream_t stream) {
   if (L.max_items == 0 || dims.hkv == 0) return hipSuccess;
   BwdParams p = make_params(dims, q, k, v, dout, lse, dvec, causal, scale, ws, L);
   if (kv_accumulate) {
@@ -318,19 +339,22 @@ hipError_t launch_dkdv_bf16(const bs_dims& dims, const void* q, const void* k, c
     p.dk = static_cast<bf16*>(dk);
     p.dv = static_cast<bf16*>(dv);
   }
-  const dim3 grid((unsigned)(L.max_items * dims.hkv));
   const bool group_order = p.group > 1;
+  const dim3 grid((unsigned)(dims.hkv * (self != nullptr ? self->items * self->splits : L.max_items)));
+  if (self != nullptr) p.self = *self;
+#define BS_DKDV(D, SELF)                                                                        \
+  do {                                                                                          \
+    if (group_order)                                                                            \
+      hipLaunchKernelGGL((dkdv_bf16_kernel<D, true, SELF>), grid, dim3(512), 0, stream, p);     \
+    else                                                                                        \
+      hipLaunchKernelGGL((dkdv_bf16_kernel<D, false, SELF>), grid, dim3(512), 0, stream, p);    \
+  } while (0)
   if (dims.head_dim == 128) {
-    if (group_order)
-      hipLaunchKernelGGL((dkdv_bf16_kernel<128, true>), grid, dim3(512), 0, stream, p);
-    else
-      hipLaunchKernelGGL((dkdv_bf16_kernel<128, false>), grid, dim3(512), 0, stream, p);
+    if (self != nullptr) BS_DKDV(128, true); else BS_DKDV(128, false);
   } else {
-    if (group_order)
-      hipLaunchKernelGGL((dkdv_bf16_kernel<64, true>), grid, dim3(512), 0, stream, p);
-    else
-      hipLaunchKernelGGL((dkdv_bf16_kernel<64, false>), grid, dim3(512), 0, stream, p);
+    if (self != nullptr) BS_DKDV(64, true); else BS_DKDV(64, false);
   }
+#undef BS_DKDV
   return hipGetLastError();
 }
 

@@ -24,7 +24,7 @@
 namespace bs {
 namespace {
 
-template <int D>
+template <int D, bool kSelf>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dq_bf16_kernel(const BwdParams p) {
   constexpr int BM = kFwdBM, BN = kFwdBN;
@@ -39,7 +39,17 @@ void dq_bf16_kernel(const BwdParams p) {
 
   WorkItem it;
   int h;  // query head; the query heads of one KV group share its K/V stream
-  if (!block_work(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
+  int slab = 0;
+  if constexpr (kSelf) {
+    __shared__ int32_t pl[kSelfMaxSegs + 8];
+    const int b = blockIdx.x / p.hq;
+    h = blockIdx.x - b * p.hq;
+    const int i = b / p.self.splits;
+    slab = b - i * p.self.splits;
+    if (!self_plan(p.self.plan, p.causal, kPlanFwd, BM, BN, i, pl, it)) return;
+  } else {
+    if (!block_work(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
+  }
   const int hk = h / p.group;
 
   const int tid = threadIdx.x;
@@ -69,13 +79,18 @@ void dq_bf16_kernel(const BwdParams p) {
     const float l = p.lse[ri];
     lse2 = l == -INFINITY ? INFINITY : l * kLog2e;
     dval = drow;
-    if (hh == 0) p.dvec_out[ri] = drow;
+    if (hh == 0 && slab == 0) p.dvec_out[ri] = drow;
   }
 
   const bf16* kbase = p.k + (int64_t)it.b_start * kvstride + (int64_t)hk * D;
   const bf16* vbase = p.v + (int64_t)it.b_start * kvstride + (int64_t)hk * D;
   const int k_len = it.b_len;
-  const int n_tiles = it.n1, n_full = it.n0;
+  const int n_full = it.n0;
+  int t_first = 0, n_tiles = it.n1;  // this workgroup's key tiles: t_first .. n_tiles - 1
+  if constexpr (kSelf) {
+    t_first = slab * it.n1 / p.self.splits;
+    n_tiles = (slab + 1) * it.n1 / p.self.splits;
+  }
 
   auto copy_tile = [&](int t, bf16* Kd, bf16* Vd) {
     const int k0 = t * BN;
@@ -95,7 +110,7 @@ void dq_bf16_kernel(const BwdParams p) {
 
   // lane bases of the row reads of K and V and the transposing reads of K
   const int rbase = swz_row_base<D>(lane), tbase = swz_tr_base<D>(lane);
-  if (n_tiles > 0) copy_tile(0, K0, V0);
+  if (n_tiles > t_first) copy_tile(t_first, K0, V0);
   wait_vmem_all();  // Q, dO fragments and tile 0
   __syncthreads();
 
@@ -155,7 +170,7 @@ void dq_bf16_kernel(const BwdParams p) {
     wait_vmem_all();  // this wave's copies of tile t+1
     __syncthreads();
   };
-  for (int t = 0; t < n_tiles; t += 2) {
+  for (int t = t_first; t < n_tiles; t += 2) {
     step(t, K0, V0, K1, V1);
     if (t + 1 < n_tiles) step(t + 1, K1, V1, K0, V0);
   }
@@ -167,6 +182,15 @@ void dq_bf16_kernel(const BwdParams p) {
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         const int col = db * 32 + a * 8;
+        if constexpr (kSelf) {
+          if (p.self.splits > 1) {
+            f32x4 y;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = dqacc[db][a * 4 + i] * p.scale;
+            *reinterpret_cast<f32x4*>(p.self.part + slab * p.total_q * qstride + off + col) = y;
+            continue;
+          }
+        }
         if (p.dq != nullptr) {
           bf16x4 x = {f2bf(dqacc[db][a * 4 + 0] * p.scale), f2bf(dqacc[db][a * 4 + 1] * p.scale),
                       f2bf(dqacc[db][a * 4 + 2] * p.scale), f2bf(dqacc[db][a * 4 + 3] * p.scale)};
@@ -189,18 +213,27 @@ void dq_bf16_kernel(const BwdParams p) {
 hipError_t launch_dq_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                           const void* out, const void* dout, const float* lse, float* dvec,
                           int causal, float scale, void* dq, float* dq_acc, const void* ws,
-                          const WsLayout& L, hipStream_t stream) {
+                          const WsLayout& L, const SelfPlan* self, hipStream_t stream) {
   if (L.max_items == 0 || dims.hq == 0) return hipSuccess;
   BwdParams p = make_params(dims, q, k, v, dout, lse, dvec, causal, scale, ws, L);
   p.o = static_cast<const bf16*>(out);
   p.dvec_out = dvec;
   p.dq = static_cast<bf16*>(dq);
   p.dq_acc = dq_acc;
+  if (self != nullptr) {
+    p.self = *self;
+    const dim3 grid((unsigned)(self->items * dims.hq * self->splits));
+    if (dims.head_dim == 128)
+      hipLaunchKernelGGL((dq_bf16_kernel<128, true>), grid, dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL((dq_bf16_kernel<64, true>), grid, dim3(256), 0, stream, p);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)(L.max_items * dims.hq));
   if (dims.head_dim == 128)
-    hipLaunchKernelGGL(dq_bf16_kernel<128>, grid, dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((dq_bf16_kernel<128, false>), grid, dim3(256), 0, stream, p);
   else
-    hipLaunchKernelGGL(dq_bf16_kernel<64>, grid, dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((dq_bf16_kernel<64, false>), grid, dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -54,11 +54,12 @@ struct FwdParams {
   int32_t hq, hkv, group;
   int32_t causal;
   float scale_log2;  // scale * log2(e)
+  SelfPlan self;     // kSelf
 };
 
 constexpr float kRescaleThreshold = 8.0f;  // log2 units
 
-template <int D>
+template <int D, bool kSelf>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fwd_bf16_kernel(const FwdParams p) {
   constexpr int BM = kFwdBM, BN = kFwdBN;
@@ -76,7 +77,17 @@ void fwd_bf16_kernel(const FwdParams p) {
 
   WorkItem it;
   int h;  // query head; the query heads of one KV group share its K/V stream
-  if (!block_work(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
+  int slab = 0;
+  if constexpr (kSelf) {
+    __shared__ int32_t pl[kSelfMaxSegs + 8];
+    const int b = blockIdx.x / p.hq;
+    h = blockIdx.x - b * p.hq;
+    const int i = b / p.self.splits;
+    slab = b - i * p.self.splits;
+    if (!self_plan(p.self.plan, p.causal, kPlanFwd, BM, BN, i, pl, it)) return;
+  } else {
+    if (!block_work(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
+  }
   const int hk = h / p.group;
 
   const int tid = threadIdx.x;
@@ -97,7 +108,12 @@ void fwd_bf16_kernel(const FwdParams p) {
   const bf16* kbase = p.k + (int64_t)it.b_start * kvstride + (int64_t)hk * D;
   const bf16* vbase = p.v + (int64_t)it.b_start * kvstride + (int64_t)hk * D;
   const int k_len = it.b_len;
-  const int n_tiles = it.n1, n_full = it.n0;
+  const int n_full = it.n0;
+  int t_first = 0, n_tiles = it.n1;  // this workgroup's key tiles: t_first .. n_tiles - 1
+  if constexpr (kSelf) {
+    t_first = slab * it.n1 / p.self.splits;
+    n_tiles = (slab + 1) * it.n1 / p.self.splits;
+  }
 
   auto copy_tile = [&](int t, bf16* Kd, bf16* Vd) {
     const int k0 = t * BN;
@@ -118,7 +134,7 @@ void fwd_bf16_kernel(const FwdParams p) {
   if (p.causal) lim_base = min(k_len, q_rel + it.diag + 1);
   lim_base -= hh * 4;  // fold the lane-half offset of the key index
 
-  if (n_tiles > 0) copy_tile(0, K0, V0);
+  if (n_tiles > t_first) copy_tile(t_first, K0, V0);
   wait_vmem_all();  // Q fragment and tile 0
   __syncthreads();
 
@@ -194,12 +210,29 @@ void fwd_bf16_kernel(const FwdParams p) {
     wait_vmem_all();  // this wave's copies of tile t+1
     __syncthreads();  // everyone's copies landed; everyone is done with (Kb, Vb)
   };
-  for (int t = 0; t < n_tiles; t += 2) {
+  for (int t = t_first; t < n_tiles; t += 2) {
     step(t, K0, V0, K1, V1);
     if (t + 1 < n_tiles) step(t + 1, K1, V1, K0, V0);
   }
 
   const float l_tot = half_sum(l_run);
+  if constexpr (kSelf) {
+    if (p.self.splits > 1) {  // (O, max, sum) of this part of the keys
+      if (!qvalid) return;
+      const int64_t all = p.total_q * p.hq, r = (it.a_start + qrow) * (int64_t)p.hq + h;
+      float* op = p.self.part + (slab * all + r) * D + hh * 4;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          *reinterpret_cast<f32x4*>(op + db * 32 + a * 8) =
+              f32x4{oacc[db][a * 4 + 0], oacc[db][a * 4 + 1], oacc[db][a * 4 + 2], oacc[db][a * 4 + 3]};
+      if (hh == 0)
+        reinterpret_cast<float2*>(p.self.part + p.self.splits * all * D)[slab * all + r] =
+            make_float2(m2, l_tot);
+      return;
+    }
+  }
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (!qvalid) return;
   const int64_t row = it.a_start + qrow;
@@ -258,7 +291,7 @@ void fwd_bf16_kernel(const FwdParams p) {
 hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, const void* v,
                            int causal, float scale, void* out, float* lse,
                            const FwdMerge* merge, const void* ws, const WsLayout& L,
-                           hipStream_t stream) {
+                           const SelfPlan* self, hipStream_t stream) {
   if (L.max_items == 0 || dims.hq == 0) return hipSuccess;
   FwdParams p;
   p.q = static_cast<const bf16*>(q);
@@ -277,11 +310,21 @@ hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, co
   p.group = dims.hq / dims.hkv;
   p.causal = causal;
   p.scale_log2 = scale * kLog2e;
+  if (self != nullptr) {
+    p.self = *self;
+    const dim3 grid((unsigned)(self->items * dims.hq * self->splits));
+    if (dims.head_dim == 128)
+      hipLaunchKernelGGL((fwd_bf16_kernel<128, true>), grid, dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL((fwd_bf16_kernel<64, true>), grid, dim3(256), 0, stream, p);
+    return hipGetLastError();
+  }
+  p.self = SelfPlan{};
   const dim3 grid((unsigned)(L.max_items * dims.hq));
   if (dims.head_dim == 128)
-    hipLaunchKernelGGL(fwd_bf16_kernel<128>, grid, dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, false>), grid, dim3(256), 0, stream, p);
   else
-    hipLaunchKernelGGL(fwd_bf16_kernel<64>, grid, dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((fwd_bf16_kernel<64, false>), grid, dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -33,33 +33,6 @@ __device__ __forceinline__ void set_status(int32_t* st, int code) {
   atomicCAS(st, 0, code);  // keeps the first error seen
 }
 
-// Segment b of the problem: query start/length, key start/length, diagonal.
-struct Seg {
-  int64_t q0, lq, k0, lk;
-  int32_t diag;
-};
-
-__device__ __forceinline__ int32_t clamp_diag(int64_t d) {
-  return (int32_t)(d < -kDiagClamp ? -kDiagClamp : (d > kDiagClamp ? kDiagClamp : d));
-}
-
-// Diagonal: key j visible to query i iff j - i <= diag.  Varlen segments are
-// aligned bottom-right (diag = len_k - len_q); packed chunk segments and single
-// chunks take it from the global positions of their first query and key.
-__device__ __forceinline__ Seg load_seg(const int32_t* cu_q, const int32_t* cu_k,
-                                        const int64_t* q_pos, const int64_t* k_pos, int32_t b,
-                                        int64_t total_q, int64_t total_k, int32_t diag_chunk) {
-  Seg s;
-  if (cu_q == nullptr) {  // chunk mode: one segment, diagonal from the offsets
-    s.q0 = 0; s.lq = total_q; s.k0 = 0; s.lk = total_k; s.diag = diag_chunk;
-  } else {
-    s.q0 = cu_q[b]; s.lq = (int64_t)cu_q[b + 1] - cu_q[b];
-    s.k0 = cu_k[b]; s.lk = (int64_t)cu_k[b + 1] - cu_k[b];
-    s.diag = q_pos == nullptr ? clamp_diag(s.lk - s.lq) : clamp_diag(q_pos[b] - k_pos[b]);
-  }
-  return s;
-}
-
 // Validates cu_seqlens, computes items per segment and their exclusive prefix into seg_off
 // (nseg + 1 entries), and the status word and item count into the header.  One workgroup
 // of kCountThreads threads; scan, carry and status are its LDS.
@@ -136,62 +109,8 @@ __device__ __forceinline__ void emit_body(
   const int32_t b = lo;
   const Seg s = load_seg(cu_q, cu_k, q_pos, k_pos, b, total_q, total_k, diag_chunk);
   const int64_t tile = i - seg_off[b];
-  const int64_t diag = s.diag;
-  WorkItem w;
-  w.seg = b; w.tile = (int32_t)tile; w.diag = s.diag; w.run0 = seg_dst[b]; w.nrun = (int32_t)(seg_off[b + 1] - seg_off[b]);
-  if (kind == kPlanFwd) {
-    const int64_t BM = tile_a, BN = tile_b;
-    const int64_t q_first = tile * BM;
-    const int64_t q_last = (q_first + BM < s.lq ? q_first + BM : s.lq) - 1;
-    const int64_t nkt = (s.lk + BN - 1) / BN;
-    int64_t n_tiles, n_full;
-    if (causal) {
-      const int64_t lim = q_last + diag;
-      n_tiles = lim < 0 ? 0 : (lim / BN + 1 < nkt ? lim / BN + 1 : nkt);
-      int64_t f = q_first + diag + 1;
-      f = f < s.lk ? f : s.lk;
-      n_full = f > 0 ? f / BN : 0;
-    } else {
-      n_tiles = nkt;
-      n_full = s.lk / BN;
-    }
-    w.a_start = (int32_t)(s.q0 + q_first);
-    w.a_rows = (int32_t)(q_last - q_first + 1);
-    w.b_start = (int32_t)s.k0;
-    w.b_len = (int32_t)s.lk;
-    w.n0 = (int32_t)n_full;
-    w.n1 = (int32_t)n_tiles;
-    w.n2 = (int32_t)n_tiles;
-  } else {
-    const int64_t BM = tile_b, BN = tile_a;
-    const int64_t k_first = tile * BN;
-    const int64_t nqt = (s.lq + BM - 1) / BM;
-    const bool in_range = k_first + BN <= s.lk;
-    int64_t first, ffirst;
-    if (causal) {
-      const int64_t r = k_first - diag;  // first query row that sees key k_first
-      first = r > s.lq - 1 ? nqt : (r > 0 ? r / BM : 0);
-      if (!in_range) {
-        ffirst = nqt;
-      } else {
-        const int64_t t = k_first + BN - 1 - diag;  // FULL needs q_first >= t
-        ffirst = t <= 0 ? 0 : (t + BM - 1) / BM;
-        ffirst = ffirst < nqt ? ffirst : nqt;
-      }
-    } else {
-      first = 0;
-      ffirst = in_range ? 0 : nqt;
-    }
-    const int64_t n_vis = nqt - first;
-    const int64_t n_masked = ffirst - first > 0 ? ffirst - first : 0;
-    w.a_start = (int32_t)(s.k0 + k_first);
-    w.a_rows = (int32_t)(s.lk - k_first < BN ? s.lk - k_first : BN);
-    w.b_start = (int32_t)s.q0;
-    w.b_len = (int32_t)s.lq;
-    w.n0 = (int32_t)first;
-    w.n1 = (int32_t)n_masked;
-    w.n2 = (int32_t)n_vis;
-  }
+  const WorkItem w = make_item(s, b, tile, causal, kind, tile_a, tile_b, seg_dst[b],
+                               seg_off[b + 1] - seg_off[b]);
   const int64_t cnt = seg_off[b + 1] - seg_off[b];
   items[seg_dst[b] + (kind == kPlanFwd ? cnt - 1 - tile : tile)] = w;
 }

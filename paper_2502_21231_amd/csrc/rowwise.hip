@@ -1,4 +1,5 @@
-// Bandwidth-bound row kernels: LSE merge, dQ finalize.
+// Bandwidth-bound row kernels: LSE merge, dQ finalize, and the sums over the parts of a split
+// chain (few_bf16.hip has its own, over a varying number of pieces).
 //
 // Each (token, head) row of head_dim elements is handled by a group of
 // head_dim/8 (bf16) or head_dim/4 (fp32) lanes, one 16-byte vector per lane,
@@ -101,6 +102,98 @@ __global__ __launch_bounds__(256) void dq_finalize_kernel(const float* __restric
     *reinterpret_cast<f32x4*>(dq + i * 4) = *reinterpret_cast<const f32x4*>(y);
 }
 
+// Forward of split chains: O = sum_s 2^(M_s - M) O_s / L, LSE = (M + log2 L) ln 2 with
+// L = sum_s 2^(M_s - M) L_s, written as bf16 or folded into the running state as the forward's
+// epilogue does.  head_dim / 4 lanes per (token, head) row; at most 8 parts, all loads first.
+constexpr int kMaxSplits = 8;
+template <int D>
+__global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restrict__ part, int splits,
+                                                          int64_t total_q, int32_t hq, bf16* out,
+                                                          float* lse, float* o_run, float* lse_run,
+                                                          int accumulate, const WsHeader* hdr) {
+  if (hdr->status != BS_DEV_OK) return;  // the segments were rejected
+  constexpr int LPR = D / 4;
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t rows = total_q * hq, row = gid / LPR;
+  const int ch = (int)(gid % LPR);
+  if (row >= rows) return;
+  const float2* stat = reinterpret_cast<const float2*>(part + splits * rows * D);
+  float m[kMaxSplits], l[kMaxSplits];
+  f32x4 x[kMaxSplits];
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int i = 0; i < kMaxSplits; ++i) {
+    m[i] = -INFINITY;
+    l[i] = 0.f;
+    x[i] = f32x4{};
+    if (i < splits) {
+      const float2 st = stat[i * rows + row];
+      m[i] = st.x;
+      l[i] = st.y;
+      x[i] = *reinterpret_cast<const f32x4*>(part + (i * rows + row) * D + ch * 4);
+    }
+    M = fmaxf(M, m[i]);
+  }
+  const float base = M == -INFINITY ? 0.f : M;
+  f32x4 o = f32x4{};
+#pragma unroll
+  for (int i = 0; i < kMaxSplits; ++i) {
+    const float w = fast_exp2(m[i] - base);
+    L += l[i] * w;
+    if (i < splits) o += x[i] * w;
+  }
+  o *= L > 0.f ? 1.f / L : 0.f;
+  const float lse2 = L > 0.f ? M + log2f(L) : -INFINITY;  // log2 units
+  const int64_t t = row / hq, li = (row - t * hq) * total_q + t;
+  bf16x4* ob = reinterpret_cast<bf16x4*>(out + row * D + ch * 4);
+  if (o_run == nullptr) {
+    *ob = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
+    if (ch == 0) lse[li] = lse2 * kLn2;
+    return;
+  }
+  const float old2 = accumulate ? lse_run[li] * kLog2e : -INFINITY;
+  const float mx = fmaxf(old2, lse2);
+  float w_old = 0.f, w_new = 0.f, lse_m = -INFINITY;
+  if (mx != -INFINITY) {
+    const float eo = fast_exp2(old2 - mx), en = fast_exp2(lse2 - mx);
+    w_old = eo / (eo + en);
+    w_new = en / (eo + en);
+    lse_m = (mx + log2f(eo + en)) * kLn2;
+  }
+  o *= w_new;
+  f32x4* orun = reinterpret_cast<f32x4*>(o_run + row * D + ch * 4);
+  if (w_old != 0.f) o += *orun * w_old;
+  if (out != nullptr) *ob = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
+  else *orun = o;
+  __builtin_amdgcn_wave_barrier();  // every lane of the row has read the old LSE
+  if (ch == 0) lse_run[li] = lse_m;
+}
+
+// out (z = 0: out0, 1: out1) = sum over the slabs, four floats per lane.
+__global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict__ part, int splits,
+                                                        int64_t n4, void* out0, void* out1,
+                                                        int accumulate_f32, const WsHeader* hdr) {
+  if (hdr->status != BS_DEV_OK) return;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  const f32x4* src = reinterpret_cast<const f32x4*>(part) + (int64_t)blockIdx.y * splits * n4 + i;
+  f32x4 x[kMaxSplits];
+#pragma unroll
+  for (int s = 0; s < kMaxSplits; ++s)
+    if (s < splits) x[s] = src[s * n4];
+  f32x4 y = x[0];
+#pragma unroll
+  for (int s = 1; s < kMaxSplits; ++s)
+    if (s < splits) y += x[s];
+  void* out = blockIdx.y == 0 ? out0 : out1;
+  if (accumulate_f32) {
+    f32x4* dst = static_cast<f32x4*>(out) + i;
+    *dst = *dst + y;
+  } else {
+    static_cast<bf16x4*>(out)[i] = bf16x4{f2bf(y[0]), f2bf(y[1]), f2bf(y[2]), f2bf(y[3])};
+  }
+}
+
 inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
 
 }  // namespace
@@ -141,6 +234,26 @@ hipError_t launch_dq_finalize(const bs_dims& dims, const float* dq_acc, void* dq
   else
     hipLaunchKernelGGL(dq_finalize_kernel<float>, dim3(blocks_for(n4)), dim3(256), 0, stream,
                        dq_acc, static_cast<float*>(dq), n4);
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd_combine(const bs_dims& dims, const SelfPlan& self, void* out, float* lse,
+                              const FwdMerge* merge, hipStream_t stream) {
+  const unsigned grid = blocks_for(dims.total_q * dims.hq * (dims.head_dim / 4));
+#define BS_COMBINE(D)                                                                           \
+  hipLaunchKernelGGL(fwd_combine_kernel<D>, dim3(grid), dim3(256), 0, stream, self.part,        \
+                     self.splits, dims.total_q, dims.hq, static_cast<bf16*>(out), lse,          \
+                     merge ? merge->o_run : nullptr, merge ? merge->lse_run : nullptr,          \
+                     merge ? merge->accumulate : 0, self.plan.hdr)
+  if (dims.head_dim == 128) BS_COMBINE(128); else BS_COMBINE(64);
+#undef BS_COMBINE
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_slabs(const float* part, int splits, int64_t n, void* out0, void* out1,
+                            int accumulate_f32, const WsHeader* hdr, hipStream_t stream) {
+  hipLaunchKernelGGL(sum_slabs_kernel, dim3(blocks_for(n / 4), out1 != nullptr ? 2 : 1), dim3(256), 0,
+                     stream, part, splits, n / 4, out0, out1, accumulate_f32, hdr);
   return hipGetLastError();
 }
 
