@@ -424,13 +424,23 @@ __device__ __forceinline__ bf16x8 lds_tr16(const bf16* tile, int off0, int off1)
 
 // Host-side launchers implemented in the .hip files (all enqueue on `stream`).
 namespace bs {
+// A second list planned by the same launch (up to kPlanFusedSegs segments): its header, the items
+// right behind it.
+constexpr int kPlanFusedSegs = 1024;
+struct PlanSecond {
+  PlanKind kind;
+  int tile_a, tile_b;
+  int64_t max_items;
+  void* hdr;
+};
+static_assert(sizeof(WsHeader) == 256, "the items of a second list start aligned");
 // Segments: cu_q/cu_k (NULL: one chunk with diagonal diag_chunk); q_pos/k_pos
 // (NULL: diagonal len_k - len_q of each segment, else q_pos[b] - k_pos[b]).
 hipError_t launch_plan(PlanKind kind, const int32_t* cu_q, const int32_t* cu_k,
                        const int64_t* q_pos, const int64_t* k_pos, int32_t num_seqs,
                        int64_t total_q, int64_t total_k, int32_t max_seqlen, int32_t diag_chunk,
                        int causal, int tile_a, int tile_b, int64_t max_items, void* ws,
-                       const WsLayout& L, hipStream_t stream);
+                       const WsLayout& L, const PlanSecond* second, hipStream_t stream);
 
 // Forward epilogue that folds the step into a running result instead of writing
 // a partial (ring steps merged as they arrive): o_run float32 [T, hq, d], lse_run

@@ -302,9 +302,15 @@ size_t extra_bytes(int op, bs_dims d, int64_t nseg, int64_t max_seqlen) {
     const size_t a = few_layout(op, d, nseg, max_seqlen).bytes;
     return a != 0 ? a : self_cfg(kSelfFwd, op, d, nseg, max_seqlen).bytes;
   }
-  const size_t a = self_cfg(kSelfDq, op, d, nseg, max_seqlen).bytes;
-  const size_t b = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen).bytes;
-  return a > b ? a : b;
+  const SelfCfg a = self_cfg(kSelfDq, op, d, nseg, max_seqlen);
+  const SelfCfg b = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen);
+  if (!a.self && !b.self && nseg <= kPlanFusedSegs) {  // the second list of one planning launch
+    PlanCfg cfg[2];
+    plans_of(op, d, cfg);
+    const int64_t items = max_items_of(cfg[1], d, nseg, is_varlen(op));
+    return sizeof(WsHeader) + align256(sizeof(WorkItem) * (size_t)items);
+  }
+  return a.bytes > b.bytes ? a.bytes : b.bytes;
 }
 
 WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
@@ -352,7 +358,7 @@ int check_ws(const WsLayout& L, const void* ws, size_t bytes) {
 hipError_t run_plan(int op, const bs_dims& d, int i, const int32_t* cu_q, const int32_t* cu_k,
                     const int64_t* q_pos, const int64_t* k_pos, int32_t num_seqs,
                     int32_t max_seqlen, int64_t q_off, int64_t k_off, int causal, void* ws,
-                    const WsLayout& L, WsLayout* Lp, hipStream_t s) {
+                    const WsLayout& L, WsLayout* Lp, hipStream_t s, const PlanSecond* second = nullptr) {
   PlanCfg cfg[2];
   plans_of(op, d, cfg);
   const bool varlen = is_varlen(op);
@@ -364,7 +370,7 @@ hipError_t run_plan(int op, const bs_dims& d, int i, const int32_t* cu_q, const 
   return launch_plan(cfg[i].kind, varlen ? cu_q : nullptr, varlen ? cu_k : nullptr,
                      packed ? q_pos : nullptr, packed ? k_pos : nullptr,
                      varlen ? num_seqs : 1, d.total_q, d.total_k, max_seqlen, (int32_t)diag,
-                     causal, cfg[i].tile_a, cfg[i].tile_b, Lp->max_items, ws, *Lp, s);
+                     causal, cfg[i].tile_a, cfg[i].tile_b, Lp->max_items, ws, *Lp, second, s);
 }
 
 // The self-planned form of a kernel for this call (NULL: by the list); buf: room for partials
@@ -516,10 +522,18 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   const SelfPlan* self = self_plan_of(kSelfDq, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen,
                                       q_off, k_off, ws, buf, &sp);
   const WsHeader* hdr = static_cast<const WsHeader*>(ws);
+  // both lists by one launch where neither kernel plans for itself and there is room for two
+  PlanCfg cfg[2];
+  plans_of(op, d, cfg);
+  const int64_t nseg = varlen ? num_seqs : 1;
+  PlanSecond second = {cfg[1].kind, cfg[1].tile_a, cfg[1].tile_b, max_items_of(cfg[1], d, nseg, varlen), buf};
+  const bool both = !f32 && buf != nullptr && nseg <= kPlanFusedSegs &&
+                    !self_cfg(kSelfDq, op, d, nseg, max_seqlen).self &&
+                    !self_cfg(kSelfDkdv, op, d, nseg, max_seqlen).self;
   if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 0, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
-                    causal, ws, L, &Lp, s),
+                    causal, ws, L, &Lp, s, both ? &second : nullptr),
            "planner launch");
   }
   {
@@ -540,7 +554,12 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   self = self_plan_of(kSelfDkdv, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
                       ws, buf, &sp);
   Lp = L;
-  if (self == nullptr) {
+  const void* list = ws;
+  if (both) {
+    list = buf;
+    Lp.sorted = sizeof(WsHeader);
+    Lp.max_items = second.max_items;
+  } else if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 1, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
                     causal, ws, L, &Lp, s),
@@ -554,7 +573,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
              "backward dK/dV launch");
     else
       BS_HIP(launch_dkdv_bf16(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate,
-                              ws, Lp, self, s),
+                              list, Lp, self, s),
              "backward dK/dV launch");
     if (self != nullptr && self->splits > 1 && kn > 0)
       BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv, kv_accumulate, hdr, s),
