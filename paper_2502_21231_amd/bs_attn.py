@@ -114,25 +114,40 @@ def _check(status: int) -> None:
         raise BsError(status, bs_last_error())
 
 
+# Small calls are bound by this module's own time, so the checks below pass their common case
+# with few attribute reads and only take a failing one apart.
+
+
 def _ptr(t) -> int | None:
-    if t is None:
-        return None
-    return t.data_ptr() if t.numel() > 0 else None
+    # NULL for None and for an empty tensor (torch gives those a null data pointer as well)
+    return None if t is None else t.data_ptr() or None
 
 
-def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+# the current stream's handle by device index (a torch internal; the public call, which builds a
+# Stream object, costs 2 us of an 8 us call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(t: torch.Tensor) -> int:
+    """Handle of the current stream of the tensor's device."""
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
+    dt = t.dtype
+    if dt is torch.bfloat16:
         return BS_BF16
-    if t.dtype == torch.float32:
+    if dt is torch.float32:
         return BS_F32
     raise TypeError(f"unsupported dtype {t.dtype}: bfloat16 or float32")
 
 
 def _need(t: torch.Tensor, name: str, dtype=None, ndim=None) -> None:
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
+            and (dtype is None or t.dtype is dtype) and (ndim is None or t.dim() == ndim)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -146,8 +161,9 @@ def _need(t: torch.Tensor, name: str, dtype=None, ndim=None) -> None:
 
 
 def make_dims(q: torch.Tensor, k: torch.Tensor | None) -> bs_dims:
-    return bs_dims(q.shape[0], k.shape[0] if k is not None else 0, q.shape[1],
-                   k.shape[1] if k is not None else 1, q.shape[2], _dtype_code(q))
+    tq, hq, d = q.shape
+    tk, hkv = k.shape[:2] if k is not None else (0, 1)
+    return bs_dims(tq, tk, hq, hkv, d, _dtype_code(q))
 
 
 def bs_attn_workspace_size(op: int, dims: bs_dims, num_seqs: int = 1, max_seqlen: int = 0) -> int:
@@ -164,9 +180,11 @@ def alloc_workspace(op: int, dims: bs_dims, device, num_seqs: int = 1, max_seqle
 
 def _qkv(q, k, v):
     _need(q, "q", ndim=3)
-    _need(k, "k", q.dtype, 3)
-    _need(v, "v", q.dtype, 3)
-    if k.shape != v.shape or k.shape[2] != q.shape[2]:
+    dt = q.dtype
+    _need(k, "k", dt, 3)
+    _need(v, "v", dt, 3)
+    ks = k.shape
+    if ks != v.shape or ks[2] != q.shape[2]:
         raise ValueError(f"shape mismatch q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
 
 
@@ -194,7 +212,7 @@ def bs_attn_varlen_fwd(q, k, v, cu_seqlens_q, cu_seqlens_k, max_seqlen: int, cau
     _check(load_library().bs_attn_varlen_fwd(
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), nseq,
         int(max_seqlen), int(bool(causal)), _scale(scale, q.shape[2]), _ptr(out), _ptr(lse),
-        _ptr(workspace), workspace.numel(), _stream(q.device)))
+        _ptr(workspace), workspace.numel(), _stream(q)))
     return out, lse
 
 
@@ -216,7 +234,7 @@ def bs_attn_varlen_fwd_noalloc(q, k, v, cu_seqlens_q, cu_seqlens_k, max_seqlen: 
     _check(load_library().bs_attn_varlen_fwd_noalloc(
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), nseq,
         int(max_seqlen), int(bool(causal)), _scale(scale, q.shape[2]), _ptr(out), _ptr(lse),
-        _stream(q.device)))
+        _stream(q)))
     return out, lse
 
 
@@ -241,7 +259,7 @@ def bs_attn_varlen_bwd(q, k, v, out, lse, dout, cu_seqlens_q, cu_seqlens_k, max_
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout),
         _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), nseq, int(max_seqlen), int(bool(causal)),
         _scale(scale, q.shape[2]), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(workspace), workspace.numel(),
-        _stream(q.device)))
+        _stream(q)))
     return dq, dk, dv
 
 
@@ -259,7 +277,7 @@ def bs_attn_chunk_fwd(q, k, v, q_pos_offset: int, k_pos_offset: int, causal: boo
     _check(load_library().bs_attn_chunk_fwd(
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), int(q_pos_offset), int(k_pos_offset),
         int(bool(causal)), _scale(scale, q.shape[2]), _ptr(out), _ptr(lse), _ptr(workspace),
-        workspace.numel(), _stream(q.device)))
+        workspace.numel(), _stream(q)))
     return out, lse
 
 
@@ -290,7 +308,7 @@ def bs_attn_chunk_bwd(q, k, v, out_merged, lse_merged, dout, q_pos_offset: int, 
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(out_merged), _ptr(lse_merged),
         _ptr(dout), int(q_pos_offset), int(k_pos_offset), int(bool(causal)),
         _scale(scale, q.shape[2]), _ptr(dq_accum), _ptr(dk), _ptr(dv), int(bool(kv_accumulate)),
-        _ptr(workspace), workspace.numel(), _stream(q.device)))
+        _ptr(workspace), workspace.numel(), _stream(q)))
     return dq_accum, dk, dv
 
 
@@ -324,7 +342,7 @@ def bs_attn_packed_chunk_fwd(q, k, v, cu_seqlens_q, cu_seqlens_k, q_pos, k_pos, 
     _check(load_library().bs_attn_packed_chunk_fwd(
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k),
         _ptr(q_pos), _ptr(k_pos), nseq, int(max_seqlen), int(bool(causal)), _scale(scale, q.shape[2]),
-        _ptr(out), _ptr(lse), _ptr(workspace), workspace.numel(), _stream(q.device)))
+        _ptr(out), _ptr(lse), _ptr(workspace), workspace.numel(), _stream(q)))
     return out, lse
 
 
@@ -354,7 +372,7 @@ def bs_attn_chunk_fwd_merge(q, k, v, q_pos_offset: int, k_pos_offset: int, o_run
     _check(load_library().bs_attn_chunk_fwd_merge(
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), int(q_pos_offset), int(k_pos_offset),
         int(bool(causal)), _scale(scale, q.shape[2]), _ptr(o_run), _ptr(lse_run),
-        int(bool(accumulate)), _ptr(out), _ptr(workspace), workspace.numel(), _stream(q.device)))
+        int(bool(accumulate)), _ptr(out), _ptr(workspace), workspace.numel(), _stream(q)))
     return o_run, lse_run, out
 
 
@@ -374,7 +392,7 @@ def bs_attn_packed_chunk_fwd_merge(q, k, v, cu_seqlens_q, cu_seqlens_k, q_pos, k
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k),
         _ptr(q_pos), _ptr(k_pos), nseq, int(max_seqlen), int(bool(causal)),
         _scale(scale, q.shape[2]), _ptr(o_run), _ptr(lse_run), int(bool(accumulate)), _ptr(out),
-        _ptr(workspace), workspace.numel(), _stream(q.device)))
+        _ptr(workspace), workspace.numel(), _stream(q)))
     return o_run, lse_run, out
 
 
@@ -406,7 +424,7 @@ def bs_attn_packed_chunk_bwd(q, k, v, out_merged, lse_merged, dout, cu_seqlens_q
         ctypes.byref(dims), _ptr(q), _ptr(k), _ptr(v), _ptr(out_merged), _ptr(lse_merged),
         _ptr(dout), _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), _ptr(q_pos), _ptr(k_pos), nseq,
         int(max_seqlen), int(bool(causal)), _scale(scale, q.shape[2]), _ptr(dq_accum), _ptr(dk),
-        _ptr(dv), int(bool(kv_accumulate)), _ptr(workspace), workspace.numel(), _stream(q.device)))
+        _ptr(dv), int(bool(kv_accumulate)), _ptr(workspace), workspace.numel(), _stream(q)))
     return dq_accum, dk, dv
 
 
@@ -416,7 +434,7 @@ def bs_dq_finalize(dq_accum, dq):
     _need(dq, "dq", None, 3)
     dims = bs_dims(dq.shape[0], 0, dq.shape[1], 1, dq.shape[2], _dtype_code(dq))
     _check(load_library().bs_dq_finalize(ctypes.byref(dims), _ptr(dq_accum), _ptr(dq),
-                                         _stream(dq.device)))
+                                         _stream(dq)))
     return dq
 
 
@@ -431,7 +449,7 @@ def bs_lse_merge(out_partials, lse_partials, out=None, lse=None):
     out = torch.empty(T, hq, d, dtype=out_partials.dtype, device=out_partials.device) if out is None else out
     lse = torch.empty(hq, T, dtype=torch.float32, device=out_partials.device) if lse is None else lse
     _check(load_library().bs_lse_merge(ctypes.byref(dims), _ptr(out_partials), _ptr(lse_partials), n,
-                                       _ptr(out), _ptr(lse), _stream(out_partials.device)))
+                                       _ptr(out), _ptr(lse), _stream(out_partials)))
     return out, lse
 
 
@@ -443,7 +461,7 @@ def bs_copy_async(dst, src):
     if dst.dtype != src.dtype or dst.numel() != src.numel():
         raise ValueError("dst and src must have the same dtype and number of elements")
     _check(load_library().bs_copy_async(_ptr(dst), _ptr(src), src.numel() * src.element_size(),
-                                        _stream(src.device)))
+                                        _stream(src)))
     return dst
 
 
@@ -472,13 +490,13 @@ def bs_softmax_xent(logits, labels, ignore_index: int = -100, grad_scale: float 
         dlogits = None
     _check(load_library().bs_softmax_xent(T, V, _dtype_code(logits), _ptr(logits), _ptr(labels),
                                           int(ignore_index), float(grad_scale), _ptr(loss), _ptr(lse),
-                                          _ptr(dlogits), _stream(dev)))
+                                          _ptr(dlogits), _stream(logits)))
     return loss, lse, dlogits
 
 
 def bs_read_device_status(workspace) -> int:
     """Synchronises and returns BS_OK or raises BsError with the device planner's status."""
-    _check(load_library().bs_read_device_status(_ptr(workspace), _stream(workspace.device)))
+    _check(load_library().bs_read_device_status(_ptr(workspace), _stream(workspace)))
     return BS_OK
 
 
@@ -497,7 +515,7 @@ def bs_attn_plan_export(op: int, dims: bs_dims, cu_seqlens_q=None, cu_seqlens_k=
         int(q_pos_offset), int(k_pos_offset), _ptr(q_pos), _ptr(k_pos), int(bool(causal)),
         _ptr(ws), ws.numel(),
         host.ctypes.data, cap, ctypes.byref(count), ctypes.byref(tm), ctypes.byref(tn),
-        _stream(ws.device)))
+        _stream(ws)))
     return host[:count.value].copy(), tm.value, tn.value
 
 
