@@ -71,8 +71,8 @@ __device__ __forceinline__ bool block_work(int b, const WsHeader* __restrict__ h
   }
   const int hx = n_heads >> 3, jb = b >> 3;
   const int g = jb / hx;
+  const WorkItem gi = items[g];  // (g is inside the list's room; read beside n_items, not after it)
   if (g >= n_items) return false;
-  const WorkItem gi = items[g];
   const int r = jb - gi.run0 * hx;  // 0 <= r < nrun * hx: this block's place in the run
   int i, hl;
   if (hx > heads_per_stream && gi.b_len >= min_rows) {
@@ -474,9 +474,10 @@ hipError_t launch_fwd_bf16(const bs_dims& dims, const void* q, const void* k, co
 hipError_t launch_fwd_combine(const bs_dims& dims, const SelfPlan& self, void* out, float* lse,
                               const FwdMerge* merge, hipStream_t stream);
 // out0 / out1 (one of them may be NULL) = sum of the slabs of n floats, slab s of out0 at part +
-// s n, of out1 behind out0's: written as bf16, or added into float32.
+// s n, of out1 behind out0's: written as bf16 or float32, or added into float32.
+enum SumOut { kSumBf16 = 0, kSumAddF32 = 1, kSumF32 = 2 };
 hipError_t launch_sum_slabs(const float* part, int splits, int64_t n, void* out0, void* out1,
-                            int accumulate_f32, const WsHeader* hdr, hipStream_t stream);
+                            SumOut mode, const WsHeader* hdr, hipStream_t stream);
 // The forward of segments of few queries (few_bf16.hip): no plan, buf of F.bytes, the header
 // only for the status word.  cu_q, cu_k of at most kFewMaxSegs segments.
 constexpr int kFewMaxSegs = 1024;
@@ -512,10 +513,12 @@ hipError_t launch_dq_f32(const bs_dims& dims, const void* q, const void* k, cons
                          const void* out, const void* dout, const float* lse, float* dvec,
                          int causal, float scale, void* dq, int dq_accumulate, const void* ws,
                          const WsLayout& L, hipStream_t stream);
+// splits > 1: each item's steps shared by that many workgroups, their sums in part (as SelfPlan).
 hipError_t launch_dkdv_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
                            const void* dout, const float* lse, const float* dvec, int causal,
                            float scale, void* dk, void* dv, int kv_accumulate, const void* ws,
-                           const WsLayout& L, hipStream_t stream);
+                           const WsLayout& L, int splits,
+                           float* part, hipStream_t stream);
 
 hipError_t launch_dq_finalize(const bs_dims& dims, const float* dq_acc, void* dq,
                               hipStream_t stream);

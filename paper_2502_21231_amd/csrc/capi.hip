@@ -254,8 +254,8 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 // parts (at most 8) with the smallest estimate in microseconds
 //   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
 //   partials' bytes, written and read, at 3 TB/s,
-// t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one),
-// the measured times of a chain on a CU.  Forward + backward, us, by the list / by this rule:
+// t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one;
+// float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.  Forward + backward, us, by the list / by this rule:
 //   512 tokens, 8/8 heads: 62 / 53 (no chain split: the three planning launches)
 //   507 tokens, 40/8: 96 / 62    854 tokens, 32/4: 140 / 76    688 tokens, 64/8: 134 / 80
 // and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
@@ -264,7 +264,8 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   SelfCfg c = {false, 1, 0, 0};
   const bool varlen = is_varlen(op);
-  if (d.dtype != BS_BF16 || (varlen && (nseg < 1 || nseg > kSelfMaxSegs))) return c;
+  const bool f32 = d.dtype == BS_F32;  // dK/dV's chains alone are split there, by the list
+  if ((f32 && k != kSelfDkdv) || (varlen && (nseg < 1 || (!f32 && nseg > kSelfMaxSegs)))) return c;
   PlanCfg cfg[2];
   plans_of(op, d, cfg);
   const bool dkdv = k == kSelfDkdv;
@@ -272,12 +273,13 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
   c.items = max_items_of(cfg[dkdv ? 1 : 0], d, nseg, varlen);
   const int64_t wgs = c.items * (dkdv ? d.hkv : d.hq);
   if (wgs < 1 || wgs > slots) return c;
-  c.self = true;
+  c.self = !f32;
   const int64_t len = dkdv ? d.total_q : d.total_k;
   const int64_t longest = varlen && max_seqlen < len ? max_seqlen : len;
-  const int64_t bm = bwd_bm(d.head_dim);
+  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim);
   const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
-  const double t = dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
+  const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)
+                 : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
   const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
   const size_t slab = rows * (d.head_dim + (k == kSelfFwd ? 2 : 0)) * sizeof(float);
   const size_t limit = k == kSelfFwd ? kFewBytes : (size_t)64 << 20;
@@ -294,10 +296,15 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
   return c;
 }
 
-// Room beyond the plan and D.  The backward's is the same for both dtypes, so that a float32
-// call's workspace also holds the bf16 call of its sizes.
+// Room beyond the plan and D.  A float32 backward asks for at least what the bf16 call of its
+// sizes does, so that its workspace also holds that call.
 size_t extra_bytes(int op, bs_dims d, int64_t nseg, int64_t max_seqlen) {
-  if (is_bwd(op)) d.dtype = BS_BF16;
+  if (is_bwd(op) && d.dtype == BS_F32) {
+    const size_t own = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen).bytes;
+    d.dtype = BS_BF16;
+    const size_t as_bf16 = extra_bytes(op, d, nseg, max_seqlen);
+    return own > as_bf16 ? own : as_bf16;
+  }
   if (!is_bwd(op)) {
     const size_t a = few_layout(op, d, nseg, max_seqlen).bytes;
     return a != 0 ? a : self_cfg(kSelfFwd, op, d, nseg, max_seqlen).bytes;
@@ -547,8 +554,8 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
                             dq_accum, ws, Lp, self, s),
              "backward dQ launch");
     if (self != nullptr && self->splits > 1 && qn > 0)
-      BS_HIP(launch_sum_slabs(self->part, self->splits, qn, direct ? dq : dq_accum, nullptr, !direct,
-                              hdr, s),
+      BS_HIP(launch_sum_slabs(self->part, self->splits, qn, direct ? dq : dq_accum, nullptr,
+                              direct ? kSumBf16 : kSumAddF32, hdr, s),
              "dQ sum launch");
   }
   self = self_plan_of(kSelfDkdv, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
@@ -567,17 +574,25 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   }
   {
     ProfScope ps(BS_KERNEL_BWD_DKDV, s);
-    if (f32)
+    if (f32) {
+      const SelfCfg c = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen);
+      const int32_t splits = buf != nullptr && kn > 0 ? c.splits : 1;
+      float* part = static_cast<float*>(buf);
       BS_HIP(launch_dkdv_f32(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate, ws,
-                             Lp, s),
+                             Lp, splits, part, s),
              "backward dK/dV launch");
-    else
+      if (splits > 1)
+        BS_HIP(launch_sum_slabs(part, splits, kn, dk, dv, kv_accumulate ? kSumAddF32 : kSumF32, hdr, s),
+               "dK/dV sum launch");
+    } else {
       BS_HIP(launch_dkdv_bf16(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate,
                               list, Lp, self, s),
              "backward dK/dV launch");
     if (self != nullptr && self->splits > 1 && kn > 0)
-      BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv, kv_accumulate, hdr, s),
+      BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv,
+                              kv_accumulate ? kSumAddF32 : kSumBf16, hdr, s),
              "dK/dV sum launch");
+    }
   }
   return ok();
 }

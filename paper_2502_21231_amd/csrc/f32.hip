@@ -20,7 +20,9 @@
 // Measured at 2,048 tokens in 5 segments, 8/4 heads, head_dim 64, against one thread per row
 // on the vector unit before: forward 1,010 -> 35 us, dQ 880 -> 49 us, dK/dV 2,300 -> 84 us
 // (28, 43 and 57 us at the library product's rate); error of dK against float64 7.4e-7 ->
-// 4.8e-7.  At 4,096 tokens, 32/8 heads, head_dim 128: 126 -> 2.5 ms for the three.
+// 4.8e-7.  At 4,096 tokens, 32/8 heads, head_dim 128: 126 -> 2.5 ms for the three.  Few key tiles
+// (a rule in capi.hip): several workgroups share a dK/dV item (751 tokens, 16/2 heads: 329 -> 165
+// us forward + backward).
 //
 // Orientation, as in the bf16 kernels: the forward and dQ compute S^T = K Q^T (a lane owns one
 // query and 16 of a block's 32 keys), dK/dV computes S = Q K^T (a lane owns one key).  The
@@ -64,6 +66,9 @@ struct F32Params {
   int32_t causal;
   int32_t kv_accumulate;  // dK, dV added into (not written over) the outputs
   float scale, scale_log2;
+  int32_t splits;  // dK/dV: workgroups of an item
+  float* part;     // and, of several, where they leave their sums
+  int64_t total_k;
 };
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -512,7 +517,8 @@ void dkdv_f32_kernel(const F32Params p) {
 
   WorkItem it;
   int hk;
-  if (!block_work(blockIdx.x, p.hdr, p.items, p.hkv, 1, kHeadMajorRowsDkdv, it, hk)) return;
+  const int slab = blockIdx.x % p.splits;
+  if (!block_work(blockIdx.x / p.splits, p.hdr, p.items, p.hkv, 1, kHeadMajorRowsDkdv, it, hk)) return;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c = lane & 31, hh = lane >> 5;
   const int qb = w & 3, role = w >> 2;
@@ -526,7 +532,9 @@ void dkdv_f32_kernel(const F32Params p) {
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
   const int q_len = it.b_len, n_vis = it.n2;
-  const int n_iter = n_vis * p.group;
+  // this workgroup's steps
+  const int i_first = slab * (n_vis * p.group) / p.splits;
+  const int n_iter = (slab + 1) * (n_vis * p.group) / p.splits;
   const int rbase = row_base<D>(lane), cbase = col_base<D>(lane);
 
   // tile i into (Qd, dOd), and lane c's row of this wave's block: its LSE or D
@@ -545,7 +553,7 @@ void dkdv_f32_kernel(const F32Params p) {
     row_raw = (role == 0 ? p.lse : p.dvec)[(int64_t)h * p.total_q + q_glob0 +
                                           (row_ok ? qb * 32 + c : 0)];
   };
-  if (n_iter > 0) copy(0, Q0, dO0);
+  if (n_iter > i_first) copy(i_first, Q0, dO0);
   wait_vmem_all();
   __syncthreads();
 
@@ -605,12 +613,12 @@ void dkdv_f32_kernel(const F32Params p) {
     }
   };
   if constexpr (kDouble) {
-    for (int i = 0; i < n_iter; i += 2) {
+    for (int i = i_first; i < n_iter; i += 2) {
       step(i, Q0, dO0, Q1, dO1);
       if (i + 1 < n_iter) step(i + 1, Q1, dO1, Q0, dO0);
     }
   } else {
-    for (int i = 0; i < n_iter; ++i) step(i, Q0, dO0, Q0, dO0);
+    for (int i = i_first; i < n_iter; ++i) step(i, Q0, dO0, Q0, dO0);
   }
   auto area = [&](int b, int rl) {
     return reinterpret_cast<char*>(rl == 0 ? Q0 : dO0) + b * 32 * D * 4;
@@ -624,8 +632,12 @@ void dkdv_f32_kernel(const F32Params p) {
 #pragma unroll
     for (int b = 1; b < 4; ++b) x += get_chunk<D>(area(b, rl), r, ch);
     if (rl == 1) x *= p.scale;
-    f32x4* dst = reinterpret_cast<f32x4*>((rl == 0 ? p.dv : p.dk) + (int64_t)(it.a_start + r) * ks +
-                                          (int64_t)hk * D + ch * 4);
+    const int64_t off = (int64_t)(it.a_start + r) * ks + (int64_t)hk * D + ch * 4;
+    if (p.splits > 1) {  // dV's slabs come behind dK's
+      *reinterpret_cast<f32x4*>(p.part + ((1 - rl) * p.splits + slab) * p.total_k * ks + off) = x;
+      continue;
+    }
+    f32x4* dst = reinterpret_cast<f32x4*>((rl == 0 ? p.dv : p.dk) + off);
     if (p.kv_accumulate) x += *dst;
     *dst = x;
   }
@@ -692,16 +704,19 @@ hipError_t launch_dq_f32(const bs_dims& dims, const void* q, const void* k, cons
 hipError_t launch_dkdv_f32(const bs_dims& dims, const void* q, const void* k, const void* v,
                            const void* dout, const float* lse, const float* dvec, int causal,
                            float scale, void* dk, void* dv, int kv_accumulate, const void* ws,
-                           const WsLayout& L, hipStream_t stream) {
+                           const WsLayout& L, int splits, float* part, hipStream_t stream) {
   if (L.max_items == 0 || dims.hkv == 0) return hipSuccess;
   F32Params p = make_params(dims, q, k, v, ws, L, causal, scale);
   p.kv_accumulate = kv_accumulate;
+  p.splits = splits;
+  p.part = part;
+  p.total_k = dims.total_k;
   p.dout = static_cast<const float*>(dout);
   p.lse = lse;
   p.dvec = const_cast<float*>(dvec);
   p.dk = static_cast<float*>(dk);
   p.dv = static_cast<float*>(dv);
-  const dim3 grid((unsigned)(L.max_items * dims.hkv));
+  const dim3 grid((unsigned)(L.max_items * dims.hkv * splits));
   if (dims.head_dim == 128) hipLaunchKernelGGL(dkdv_f32_kernel<128>, grid, dim3(kThreads), 0, stream, p);
   else hipLaunchKernelGGL(dkdv_f32_kernel<64>, grid, dim3(kThreads), 0, stream, p);
   return hipGetLastError();

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restric
 // out (z = 0: out0, 1: out1) = sum over the slabs, four floats per lane.
 __global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict__ part, int splits,
                                                         int64_t n4, void* out0, void* out1,
-                                                        int accumulate_f32, const WsHeader* hdr) {
+                                                        int mode, const WsHeader* hdr) {
   if (hdr->status != BS_DEV_OK) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
@@ -186,9 +186,9 @@ __global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict_
   for (int s = 1; s < kMaxSplits; ++s)
     if (s < splits) y += x[s];
   void* out = blockIdx.y == 0 ? out0 : out1;
-  if (accumulate_f32) {
+  if (mode != kSumBf16) {
     f32x4* dst = static_cast<f32x4*>(out) + i;
-    *dst = *dst + y;
+    *dst = mode == kSumAddF32 ? *dst + y : y;
   } else {
     static_cast<bf16x4*>(out)[i] = bf16x4{f2bf(y[0]), f2bf(y[1]), f2bf(y[2]), f2bf(y[3])};
   }
@@ -251,9 +251,9 @@ hipError_t launch_fwd_combine(const bs_dims& dims, const SelfPlan& self, void* o
 }
 
 hipError_t launch_sum_slabs(const float* part, int splits, int64_t n, void* out0, void* out1,
-                            int accumulate_f32, const WsHeader* hdr, hipStream_t stream) {
+                            SumOut mode, const WsHeader* hdr, hipStream_t stream) {
   hipLaunchKernelGGL(sum_slabs_kernel, dim3(blocks_for(n / 4), out1 != nullptr ? 2 : 1), dim3(256), 0,
-                     stream, part, splits, n / 4, out0, out1, accumulate_f32, hdr);
+                     stream, part, splits, n / 4, out0, out1, (int)mode, hdr);
   return hipGetLastError();
 }
 

@@ -54,3 +54,23 @@ def test_f32_chunk_edges(gpu, d, tq, tk, diag):
     want = A.chunk_bwd(q, k, v, o_in, lse_in, do, 1000 + diag, 1000, True, sc)
     for name, g, r in zip(("dQ", "dK", "dV"), acc, want):
         check_close(name, f64(g), np.asarray(r) + 0.5, 1e-5, rel=1e-5)
+
+
+@pytest.mark.parametrize("d,hq,hkv,causal", [(64, 8, 1, True), (128, 6, 2, False)])
+def test_f32_split_dkdv(gpu, d, hq, hkv, causal):
+    """Few key tiles and a group of heads: each dK/dV item's steps are shared by several workgroups
+    (the workspace has room for their sums), or not (a workspace without it)."""
+    lens = [500, 1, 333]
+    T, sc = sum(lens), scale_for(d)
+    cu = torch.from_numpy(inputs.cu_seqlens(lens))
+    q, k, v, do = make_qkv(23, T, T, hq, hkv, d, torch.float32)
+    o_ref, lse_ref = A.varlen_fwd(q, k, v, cu.numpy(), cu.numpy(), causal, sc)
+    o_in, lse_in = torch.from_numpy(o_ref).float(), torch.from_numpy(lse_ref).float()
+    want = A.varlen_bwd(q, k, v, o_in, lse_in, do, cu.numpy(), cu.numpy(), causal, sc)
+    qg, kg, vg, dog, cug, og, lg = to_gpu(q, k, v, do, cu, o_in, lse_in)
+    size = B.bs_attn_workspace_size(B.BS_OP_VARLEN_BWD, B.make_dims(qg, kg), 3, 500)
+    for bytes_ in (size, size - 4096):
+        ws = torch.empty(bytes_, dtype=torch.uint8, device=gpu)
+        got = B.bs_attn_varlen_bwd(qg, kg, vg, og, lg, dog, cug, cug, 500, causal, sc, workspace=ws)
+        for name, g, r in zip(("dQ", "dK", "dV"), got, want):
+            check_close(name, f64(g), r, 1e-5, rel=1e-5)
