@@ -32,7 +32,12 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const T* __restrict__ pa
                                                         float* __restrict__ lse) {
   typedef typename Vec<T>::type V;
   constexpr int LPR = D / Vec<T>::N;  // lanes per row
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // Blocks are dealt to the 8 XCDs round-robin; each XCD takes a contiguous eighth of the rows,
+  // so that a line of the LSE (one head, 32 tokens) comes into one XCD's L2, not into eight
+  // (bf16, n = 8, 8,192 tokens, 32 heads: 108.2 -> 103.4 us, 5.9 TB/s; n = 2, 48 heads: 55.7 ->
+  // 49.8).
+  const int64_t blk = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int64_t gid = blk * blockDim.x + threadIdx.x;
   const int64_t row = gid / LPR;      // row = t * hq + h
   const int part = gid % LPR;
   if (row >= rows) return;
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const T* __restrict__ pa
   V y;
 #pragma unroll
   for (int i = 0; i < Vec<T>::N; ++i) y[i] = from_f<T>(acc[i] * inv);
-  *reinterpret_cast<V*>(out + row * D + part * Vec<T>::N) = y;
+  __builtin_nontemporal_store(y, reinterpret_cast<V*>(out + row * D + part * Vec<T>::N));
   if (part == 0) lse[(int64_t)h * total_q + t] = m == -INFINITY ? -INFINITY : m + logf(wsum);
 }
 
@@ -203,7 +208,7 @@ hipError_t launch_lse_merge(const bs_dims& dims, const void* out_parts, const fl
   const int64_t rows = dims.total_q * dims.hq;
   if (rows == 0) return hipSuccess;
   const int vec = dims.dtype == BS_BF16 ? 8 : 4;
-  const unsigned grid = blocks_for(rows * (dims.head_dim / vec));
+  const unsigned grid = (blocks_for(rows * (dims.head_dim / vec)) + 7) / 8 * 8;
 #define BS_MERGE_U(T, D, U)                                                                   \
   hipLaunchKernelGGL((lse_merge_kernel<T, D, U>), dim3(grid), dim3(256), 0, stream,          \
                      static_cast<const T*>(out_parts), lse_parts, n, rows, dims.hq,           \
