@@ -39,6 +39,11 @@
 // transposing reads alike), double-buffered in distinct arrays: the copy of the next tile
 // is issued before the current one is consumed and waited for after it, one full barrier
 // per tile.  Rows past a segment are fetched from its last valid row and never contribute.
+//
+// kSelf (grids that the chip holds at once; the rule and its measurements are in capi.hip): a
+// workgroup finds its item from cu_seqlens and takes one of `splits` equal parts of its steps
+// (query tiles x heads of the group), and leaves its float32 dK and dV when the item is
+// shared.
 #include <type_traits>
 
 #include "bwd_common.hpp"

@@ -19,6 +19,10 @@
 // This file is compiled with the backend's max-ILP scheduling strategy (build.py), which
 // schedules this kernel's loop about 2-3% faster than the default; the other kernels keep
 // the default.
+//
+// kSelf (grids that the chip holds at once; the rule and its measurements are in capi.hip): a
+// workgroup finds its item from cu_seqlens and takes one of `splits` equal parts of its key
+// tiles, and leaves its float32 dQ when the item is shared.
 #include "bwd_common.hpp"
 
 namespace bs {

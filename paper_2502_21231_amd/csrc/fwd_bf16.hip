@@ -34,6 +34,10 @@
 // is skipped on almost every tile; p then stays below 2^8, which neither the
 // bf16 P nor the fp32 sums mind, and O = acc / l, LSE = (m + log2 l) ln 2 use
 // the same m.
+//
+// kSelf (grids that the chip holds at once; the rule and its measurements are in capi.hip): a
+// workgroup finds its item from cu_seqlens and takes one of `splits` equal parts of its key
+// tiles, and leaves its (O, max, sum) in float32 when the item is shared.
 #include "attn.hpp"
 
 namespace bs {
