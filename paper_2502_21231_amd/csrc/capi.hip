@@ -250,7 +250,12 @@ struct SelfCfg {
 enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 
 // The rule, from the sizes: at most as many workgroups as the chip holds at once (two per CU for
-// the forward and dQ, one for dK/dV: then the list's order does not matter), and the number of
+// the forward and dQ, one for dK/dV: then the list's order does not matter), or less than half
+// as many again where no segment is longer than 512 (forward + backward, by the list / so: 1,343
+// tokens, 32/32 heads, 86 us / 80; 899, 40/8, 67 / 59; 477, 32/32, 43 / 39; with more or longer
+// tiles the last of them start too late without the order: 741 tokens, 64/8, 768 workgroups,
+// 110.8 / 112.1; 1,742, 32/32, longest 913, 109 / 112; 5,280, 16/16, longest 1,181, 159 / 175);
+// and the number of
 // parts (at most 8) with the smallest estimate in microseconds
 //   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
 //   partials' bytes, written and read, at 3 TB/s,
@@ -261,6 +266,7 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 // and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
 // subsequences, 16/2 heads: 538 / 346.  Partials: 16 MiB at most in the forward (what the
 // allocation-free entry point holds), 64 MiB in the backward.
+constexpr int64_t kSelfShort = 512;
 SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   SelfCfg c = {false, 1, 0, 0};
   const bool varlen = is_varlen(op);
@@ -272,10 +278,11 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
   const int64_t slots = dkdv ? 256 : 512;
   c.items = max_items_of(cfg[dkdv ? 1 : 0], d, nseg, varlen);
   const int64_t wgs = c.items * (dkdv ? d.hkv : d.hq);
-  if (wgs < 1 || wgs > slots) return c;
-  c.self = !f32;
   const int64_t len = dkdv ? d.total_q : d.total_k;
   const int64_t longest = varlen && max_seqlen < len ? max_seqlen : len;
+  const bool more = !f32 && longest <= kSelfShort;
+  if (wgs < 1 || (more ? 2 * wgs >= 3 * slots : wgs > slots)) return c;
+  c.self = !f32;
   const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim);
   const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
   const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)

@@ -65,6 +65,30 @@ def test_split_varlen_matches_oracle(gpu, lens, hq, hkv, d, causal):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv", [
+    ([512, 1, 0, 129, 33], 64, 32),     # 11 items: 704 and 352 workgroups, the longest allowed
+    ([40, 300, 64, 7], 94, 47),         # 8 items: 752 and 376, just below 768 and 384
+    ([40, 300, 64, 7], 96, 48),         # 768 and 384: by the list
+    ([513, 100, 29], 64, 32),           # 9 items: 576 and 288, but one segment is too long
+])
+def test_more_workgroups_than_slots(gpu, lens, hq, hkv, d):
+    """Grids somewhat above what the chip holds at once, on both sides of the rule's lines."""
+    T, mx, sc = sum(lens), max(lens), scale_for(d)
+    cu = torch.from_numpy(inputs.cu_seqlens(lens))
+    q, k, v, do = make_qkv(64, T, T, hq, hkv, d, torch.bfloat16)
+    qg, kg, vg, dog, cug = to_gpu(q, k, v, do, cu)
+    o_ref, lse_ref = A.varlen_fwd(q, k, v, cu.numpy(), cu.numpy(), True, sc)
+    o_in, lse_in = torch.from_numpy(o_ref).to(torch.bfloat16), torch.from_numpy(lse_ref).float()
+    want = A.varlen_bwd(q, k, v, o_in, lse_in, do, cu.numpy(), cu.numpy(), True, sc)
+    out, lse = B.bs_attn_varlen_fwd(qg, kg, vg, cug, cug, mx, True, sc)
+    check_close("O", f64(out), o_ref, BF["o"], bf16_out=True)
+    check_lse("LSE", f64(lse), lse_ref, BF["lse"])
+    got = B.bs_attn_varlen_bwd(qg, kg, vg, o_in.cuda(), lse_in.cuda(), dog, cug, cug, mx, True, sc)
+    for name, g, r in zip(("dQ", "dK", "dV"), got, want):
+        check_close(name, f64(g), r, BF["grad"], bf16_out=True)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("tq,tk,diag", [(700, 1300, 600), (130, 2000, 900), (900, 500, -300)])
 def test_split_chunks_fold_and_accumulate(gpu, d, tq, tk, diag):
     """Ring steps: the forward folded into a running state (replaced, accumulated, written out in
