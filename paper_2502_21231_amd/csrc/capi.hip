@@ -289,6 +289,7 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
                  : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
   const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
   const size_t slab = rows * (d.head_dim + (k == kSelfFwd ? 2 : 0)) * sizeof(float);
+  if (rows == 0) return c;  // no output rows (all segments lack queries, or keys): nothing to share
   const size_t limit = k == kSelfFwd ? kFewBytes : (size_t)64 << 20;
   double best = 0;
   for (int32_t s = 1; s <= 8 && s <= chain && (s == 1 || s * slab <= limit); ++s) {
@@ -560,7 +561,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
       BS_HIP(launch_dq_bf16(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : nullptr,
                             dq_accum, ws, Lp, self, s),
              "backward dQ launch");
-    if (self != nullptr && self->splits > 1 && qn > 0)
+    if (self != nullptr && self->splits > 1)
       BS_HIP(launch_sum_slabs(self->part, self->splits, qn, direct ? dq : dq_accum, nullptr,
                               direct ? kSumBf16 : kSumAddF32, hdr, s),
              "dQ sum launch");
@@ -583,7 +584,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
     ProfScope ps(BS_KERNEL_BWD_DKDV, s);
     if (f32) {
       const SelfCfg c = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen);
-      const int32_t splits = buf != nullptr && kn > 0 ? c.splits : 1;
+      const int32_t splits = buf != nullptr ? c.splits : 1;
       float* part = static_cast<float*>(buf);
       BS_HIP(launch_dkdv_f32(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate, ws,
                              Lp, splits, part, s),
@@ -595,10 +596,10 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
       BS_HIP(launch_dkdv_bf16(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate,
                               list, Lp, self, s),
              "backward dK/dV launch");
-    if (self != nullptr && self->splits > 1 && kn > 0)
-      BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv,
-                              kv_accumulate ? kSumAddF32 : kSumBf16, hdr, s),
-             "dK/dV sum launch");
+      if (self != nullptr && self->splits > 1)
+        BS_HIP(launch_sum_slabs(self->part, self->splits, kn, dk, dv,
+                                kv_accumulate ? kSumAddF32 : kSumBf16, hdr, s),
+               "dK/dV sum launch");
     }
   }
   return ok();

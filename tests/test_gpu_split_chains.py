@@ -138,3 +138,35 @@ def test_split_bad_cu_seqlens_writes_nothing(gpu):
                 B.bs_read_device_status(ws)
             assert f"code {code}" in str(e.value)
             assert all(torch.all(x == 7.0) for x in outs)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (4, 1)])
+@pytest.mark.parametrize("lk", [[2048], [2000, 1000], [0, 5000, 3]])
+def test_no_queries_over_long_keys(gpu, lk, hq, hkv, dtype):
+    """Segments that all lack queries (a rank with none of this batch's): nothing to write in the
+    forward, a running state without rows left alone, dK = dV = 0."""
+    d, n, mx, sc = 128, len(lk), max(lk), scale_for(128)
+    cq = torch.zeros(n + 1, dtype=torch.int32, device=gpu)
+    ck = torch.from_numpy(inputs.cu_seqlens(lk)).cuda()
+    pos = torch.zeros(n, dtype=torch.int64, device=gpu)
+    q, k, v, do = to_gpu(*make_qkv(65, 0, sum(lk), hq, hkv, d, dtype))
+    dims = B.make_dims(q, k)
+    ws = B.alloc_workspace(B.BS_OP_VARLEN_FWD, dims, gpu, n, mx)
+    out, lse = B.bs_attn_varlen_fwd(q, k, v, cq, ck, mx, True, sc, workspace=ws)
+    assert out.shape == (0, hq, d) and lse.shape == (hq, 0)
+    assert B.bs_read_device_status(ws) == B.BS_OK
+    B.bs_attn_varlen_fwd_noalloc(q, k, v, cq, ck, mx, True, sc)
+    ws = B.alloc_workspace(B.BS_OP_PACKED_CHUNK_FWD, dims, gpu, n, mx)
+    B.bs_attn_packed_chunk_fwd(q, k, v, cq, ck, pos, pos, mx, True, sc, workspace=ws)
+    assert B.bs_read_device_status(ws) == B.BS_OK
+    o_run = torch.empty(0, hq, d, device=gpu)
+    for accumulate in (False, True):
+        B.bs_attn_packed_chunk_fwd_merge(q, k, v, cq, ck, pos, pos, mx, o_run, lse, accumulate, True,
+                                         sc, out=out, workspace=ws)
+        assert B.bs_read_device_status(ws) == B.BS_OK
+    dk, dv = torch.full_like(k, 7.0), torch.full_like(v, 7.0)
+    ws = B.alloc_workspace(B.BS_OP_VARLEN_BWD, dims, gpu, n, mx)
+    B.bs_attn_varlen_bwd(q, k, v, out, lse, do, cq, ck, mx, True, sc, dk=dk, dv=dv, workspace=ws)
+    assert B.bs_read_device_status(ws) == B.BS_OK
+    assert not dk.any() and not dv.any()
