@@ -178,8 +178,8 @@ __device__ __forceinline__ WorkItem make_item(const Seg& s, int32_t b, int64_t t
 }
 
 // What a kernel needs to find its own work item (no planning launch), for grids that the chip
-// holds at once: the order of the list does not matter then, and a workgroup reads cu_seqlens
-// about as fast as a work item.
+// holds at once (about: the rule is in capi.hip): a workgroup reads cu_seqlens about as fast as a
+// work item.
 constexpr int kSelfMaxSegs = 256;
 struct PlanArgs {
   const int32_t* cu_q;  // NULL: one chunk with diagonal diag_chunk
@@ -190,13 +190,41 @@ struct PlanArgs {
   int64_t total_q, total_k;
   int32_t num_seqs, max_seqlen, diag_chunk;
 };
+// LDS of self_plan.
+struct SelfLds {
+  uint2 seg[kSelfMaxSegs];  // size (len_q + len_k) and items of each segment
+  int32_t bad, n;
+  int32_t found, slot;  // the segment of item i, and its first slot
+};
 
-// Item i of the unordered list (segments in order, tiles ascending) for a workgroup of at least
-// kSelfMaxSegs threads; false when there is none or cu_seqlens is rejected.  Block 0 writes the
-// header.  lds: kSelfMaxSegs + 8 int32.
+// Head and list slot (x splits) of block b.  With `own` (and n_heads a multiple of 8) each XCD owns
+// a contiguous eighth of the heads, as block_work deals them, so that the query heads of a KV group
+// read its K and V into one L2; otherwise the heads go round.  `own` where no chain is split, as in
+// the list (forward, 512 queries over 16K keys, 32/32 heads, head_dim 128: round 239 us, own 230),
+// and of the split ones where heads share 256-byte rows (6 segments of 12..28 queries over 3..9K
+// keys, 48/8 heads, head_dim 128: round 148, own 114).  Split chains of head_dim 64, or without a
+// group, do not gain (256 queries over 8K keys, 32/4 heads, head_dim 64: round 40.7, own 43.2; 3
+// queries over 6.4K keys, 32/32: 26.7, 28.7).
+__device__ __forceinline__ int self_block(int b, int n_heads, bool own, int& head) {
+  if (!own || (n_heads & 7) != 0) {
+    const int i = b / n_heads;
+    head = b - i * n_heads;
+    return i;
+  }
+  const int hx = n_heads >> 3, jb = b >> 3, i = jb / hx;
+  head = (b & 7) * hx + (jb - i * hx);
+  return i;
+}
+
+// Item i of the list, in the planner's order (larger segments first, a segment's longest chains
+// first), for a workgroup of at least kSelfMaxSegs threads; false when there is none or cu_seqlens
+// is rejected.  The order matters on grids that the chip holds at once too: it decides which
+// workgroups share a CU (forward, us, planning launch and list / segments and tiles as they come /
+// in order: 300 queries each over 2.3K and 6.3K keys, 48/8 heads, head_dim 64, 74 / 84 / 70; 4,096
+// tokens, 12/4, head_dim 64, 54 / 57 / 49).  Block 0 writes the header.
 __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kind, int tile_a,
-                                          int tile_b, int32_t i, int32_t* lds, WorkItem& it) {
-  const int tid = threadIdx.x, lane = tid & 63;
+                                          int tile_b, int32_t i, SelfLds& lds, WorkItem& it) {
+  const int tid = threadIdx.x;
   if (a.cu_q == nullptr) {
     const Seg s = load_seg(nullptr, nullptr, nullptr, nullptr, 0, a.total_q, a.total_k, a.diag_chunk);
     const int32_t n = (int32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a);
@@ -205,54 +233,49 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
       a.hdr->n_items = n;
     }
     if (i >= n) return false;
-    it = make_item(s, 0, i, causal, kind, tile_a, tile_b, 0, n);
+    it = make_item(s, 0, kind == kPlanFwd ? n - 1 - i : i, causal, kind, tile_a, tile_b, 0, n);
     return true;
   }
-  int32_t* pre = lds;                     // items before each segment
-  int32_t* wsum = lds + kSelfMaxSegs + 1; // of each of the first four waves
-  int32_t* bad = wsum + 4;
-  if (tid == 0) *bad = BS_DEV_OK;
+  if (tid == 0) lds.bad = BS_DEV_OK;
   __syncthreads();
-  int32_t cnt = 0;
+  uint2 mine = {0, 0};
   if (tid < a.num_seqs) {
     const Seg s = load_seg(a.cu_q, a.cu_k, nullptr, nullptr, tid, a.total_q, a.total_k, 0);
-    if (s.lq < 0 || s.lk < 0) atomicCAS(bad, 0, BS_DEV_NOT_MONOTONE);
-    else if (s.lq > a.max_seqlen || s.lk > a.max_seqlen) atomicCAS(bad, 0, BS_DEV_TOO_LONG);
-    else cnt = (int32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a);
+    if (s.lq < 0 || s.lk < 0) atomicCAS(&lds.bad, 0, BS_DEV_NOT_MONOTONE);
+    else if (s.lq > a.max_seqlen || s.lk > a.max_seqlen) atomicCAS(&lds.bad, 0, BS_DEV_TOO_LONG);
+    else mine = {(uint32_t)(s.lq + s.lk), (uint32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a)};
+    lds.seg[tid] = mine;
   }
   if (tid == 0) {
-    if (a.cu_q[0] != 0 || a.cu_k[0] != 0) atomicExch(bad, BS_DEV_BAD_FIRST);
+    if (a.cu_q[0] != 0 || a.cu_k[0] != 0) atomicExch(&lds.bad, BS_DEV_BAD_FIRST);
     else if (a.cu_q[a.num_seqs] != a.total_q || a.cu_k[a.num_seqs] != a.total_k)
-      atomicExch(bad, BS_DEV_BAD_TOTAL);
-  }
-  int32_t run = cnt;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t x = __shfl_up(run, off);
-    if (lane >= off) run += x;
-  }
-  if (tid < kSelfMaxSegs && lane == 63) wsum[tid >> 6] = run;
-  __syncthreads();
-  if (tid < kSelfMaxSegs) {
-    int32_t at = run - cnt;
-    for (int w = 0; w < (tid >> 6); ++w) at += wsum[w];
-    if (tid <= a.num_seqs) pre[tid] = at;
-    if (tid == kSelfMaxSegs - 1 && a.num_seqs == kSelfMaxSegs) pre[kSelfMaxSegs] = at + cnt;
+      atomicExch(&lds.bad, BS_DEV_BAD_TOTAL);
   }
   __syncthreads();
-  const int32_t code = *bad, n = pre[a.num_seqs];
+  if (tid < kSelfMaxSegs) {  // slots before this segment: one broadcast read per segment
+    uint32_t at = 0, n = 0;
+#pragma unroll 4
+    for (int j = 0; j < a.num_seqs; ++j) {
+      const uint2 o = lds.seg[j];
+      n += o.y;
+      at += o.x > mine.x || (o.x == mine.x && j < tid) ? o.y : 0;
+    }
+    if (tid == 0) lds.n = (int32_t)n;
+    if (tid < a.num_seqs && (uint32_t)i - at < mine.y) {  // (at most one segment)
+      lds.found = tid;
+      lds.slot = (int32_t)at;
+    }
+  }
+  __syncthreads();
+  const int32_t code = lds.bad, n = lds.n;
   if (blockIdx.x == 0 && tid == 0) {
     a.hdr->status = code;
     a.hdr->n_items = code == BS_DEV_OK ? n : 0;
   }
   if (code != BS_DEV_OK || i >= n) return false;  // uniform
-  int32_t lo = 0, hi = a.num_seqs - 1;
-  while (lo < hi) {  // the last segment whose items begin at or before i (empty ones skipped)
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if (pre[mid] <= i) lo = mid; else hi = mid - 1;
-  }
-  const Seg s = load_seg(a.cu_q, a.cu_k, a.q_pos, a.k_pos, lo, a.total_q, a.total_k, 0);
-  it = make_item(s, lo, i - pre[lo], causal, kind, tile_a, tile_b, pre[lo], pre[lo + 1] - pre[lo]);
+  const int32_t b = lds.found, at = lds.slot, cnt = (int32_t)lds.seg[b].y;
+  const Seg s = load_seg(a.cu_q, a.cu_k, a.q_pos, a.k_pos, b, a.total_q, a.total_k, 0);
+  it = make_item(s, b, kind == kPlanFwd ? cnt - 1 - (i - at) : i - at, causal, kind, tile_a, tile_b, at, cnt);
   return true;
 }
 

@@ -250,22 +250,19 @@ struct SelfCfg {
 enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 
 // The rule, from the sizes: at most as many workgroups as the chip holds at once (two per CU for
-// the forward and dQ, one for dK/dV: then the list's order does not matter), or less than half
-// as many again where no segment is longer than 512 (forward + backward, by the list / so: 1,343
-// tokens, 32/32 heads, 86 us / 80; 899, 40/8, 67 / 59; 477, 32/32, 43 / 39; with more or longer
-// tiles the last of them start too late without the order: 741 tokens, 64/8, 768 workgroups,
-// 110.8 / 112.1; 1,742, 32/32, longest 913, 109 / 112; 5,280, 16/16, longest 1,181, 159 / 175);
-// and the number of
-// parts (at most 8) with the smallest estimate in microseconds
+// the forward and dQ, one for dK/dV), or less than half as many again where no segment is longer
+// than 512; and the number of parts (at most 8) with the smallest estimate in microseconds
 //   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
 //   partials' bytes, written and read, at 3 TB/s,
 // t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one;
-// float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.  Forward + backward, us, by the list / by this rule:
-//   512 tokens, 8/8 heads: 62 / 53 (no chain split: the three planning launches)
-//   507 tokens, 40/8: 96 / 62    854 tokens, 32/4: 140 / 76    688 tokens, 64/8: 134 / 80
+// float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.
+// Forward + backward, us, by the list / so:
+//   512 tokens, 8/8 heads: 55 / 49    505, 64/8: 99 / 68    628, 32/4: 134 / 70    864, 32/32: 61 / 56
 // and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
-// subsequences, 16/2 heads: 538 / 346.  Partials: 16 MiB at most in the forward (what the
-// allocation-free entry point holds), 64 MiB in the backward.
+// subsequences, 16/2 heads: 538 / 346.  Beyond the lines the gain falls off (2,671 tokens, 32/32,
+// 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
+// Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
+// the backward.
 constexpr int64_t kSelfShort = 512;
 SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   SelfCfg c = {false, 1, 0, 0};

@@ -76,9 +76,8 @@ void dkdv_bf16_kernel(const BwdParams p) {
   int hk;  // KV head; each reads the Q/dO stream of its own query heads
   int slab = 0;
   if constexpr (kSelf) {
-    __shared__ int32_t pl[kSelfMaxSegs + 8];
-    const int b = blockIdx.x / p.hkv;
-    hk = blockIdx.x - b * p.hkv;
+    __shared__ SelfLds pl;
+    const int b = self_block(blockIdx.x, p.hkv, p.self.splits == 1, hk);
     const int i = b / p.self.splits;
     slab = b - i * p.self.splits;
     if (!self_plan(p.self.plan, p.causal, kPlanBwd, BN, BM, i, pl, it)) return;

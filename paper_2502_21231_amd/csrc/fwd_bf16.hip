@@ -83,9 +83,8 @@ void fwd_bf16_kernel(const FwdParams p) {
   int h;  // query head; the query heads of one KV group share its K/V stream
   int slab = 0;
   if constexpr (kSelf) {
-    __shared__ int32_t pl[kSelfMaxSegs + 8];
-    const int b = blockIdx.x / p.hq;
-    h = blockIdx.x - b * p.hq;
+    __shared__ SelfLds pl;
+    const int b = self_block(blockIdx.x, p.hq, p.self.splits == 1 || (D == 128 && p.group > 1), h);
     const int i = b / p.self.splits;
     slab = b - i * p.self.splits;
     if (!self_plan(p.self.plan, p.causal, kPlanFwd, BM, BN, i, pl, it)) return;

@@ -118,6 +118,33 @@ def test_split_chunks_fold_and_accumulate(gpu, d, tq, tk, diag):
         check_close(name, f64(g), np.asarray(r) + 0.5, BF["grad"])
 
 
+@pytest.mark.parametrize("n", [65, 255, 256, 257])
+def test_many_segments(gpu, n):
+    """Segments beyond the first wave, and a full table of 256 (257: by the list), empty ones and
+    equal sizes among them: every segment's tiles are found once, whatever its place."""
+    hq, hkv, d, sc = 1, 1, 64, scale_for(64)
+    lens = [int(x) for x in np.random.default_rng(n).integers(0, 40, n)]
+    lens[0], lens[63], lens[64], lens[n - 1] = 0, 200, 7, 131
+    lens[n // 2] = 0
+    T, mx = sum(lens), max(lens)
+    cu = torch.from_numpy(inputs.cu_seqlens(lens))
+    q, k, v, do = make_qkv(66, T, T, hq, hkv, d, torch.bfloat16)
+    qg, kg, vg, dog, cug = to_gpu(q, k, v, do, cu)
+    o_ref, lse_ref = A.varlen_fwd(q, k, v, cu.numpy(), cu.numpy(), True, sc)
+    o_in, lse_in = torch.from_numpy(o_ref).to(torch.bfloat16), torch.from_numpy(lse_ref).float()
+    want = A.varlen_bwd(q, k, v, o_in, lse_in, do, cu.numpy(), cu.numpy(), True, sc)
+    pos = torch.zeros(n, dtype=torch.int64, device=gpu)  # (the varlen entry may take few_bf16.hip)
+    out, lse = torch.full_like(qg, 7.0), torch.full((hq, T), 7.0, device=gpu)
+    B.bs_attn_packed_chunk_fwd(qg, kg, vg, cug, cug, pos, pos, mx, True, sc, out=out, lse=lse)
+    check_close("O", f64(out), o_ref, BF["o"], bf16_out=True)
+    check_lse("LSE", f64(lse), lse_ref, BF["lse"])
+    got = [torch.full_like(x, 7.0) for x in (qg, kg, vg)]
+    B.bs_attn_varlen_bwd(qg, kg, vg, o_in.cuda(), lse_in.cuda(), dog, cug, cug, mx, True, sc, dq=got[0],
+                         dk=got[1], dv=got[2])
+    for name, g, r in zip(("dQ", "dK", "dV"), got, want):
+        check_close(name, f64(g), r, BF["grad"], bf16_out=True)
+
+
 def test_split_bad_cu_seqlens_writes_nothing(gpu):
     q, k, v, do = make_qkv(64, 900, 900, 2, 1, 128, torch.bfloat16)
     qg, kg, vg, dog = to_gpu(q, k, v, do)
