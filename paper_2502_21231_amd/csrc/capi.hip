@@ -179,24 +179,91 @@ int check_scale(float s) {
   return BS_OK;
 }
 
+// How a bf16 kernel of few workgroups runs: by its own plan (no list), each work item's chain of
+// tiles split over `splits` workgroups.
+struct SelfCfg {
+  bool self;
+  int32_t splits;
+  int64_t items, wgs;
+  size_t bytes;  // of the partials (0: none)
+  double us;     // the estimate below
+};
+enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
+
+// The rule, from the sizes: at most as many workgroups as the chip holds at once (two per CU for
+// the forward and dQ, one for dK/dV), or less than half as many again where no segment is longer
+// than 512; and the number of parts (at most 8) with the smallest estimate in microseconds
+//   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
+//   partials' bytes, written and read, at 3 TB/s,
+// t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one;
+// float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.
+// Forward + backward, us, by the list / so:
+//   512 tokens, 8/8 heads: 55 / 49    505, 64/8: 99 / 68    628, 32/4: 134 / 70    864, 32/32: 61 / 56
+// and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
+// subsequences, 16/2 heads: 538 / 346.  Beyond the lines the gain falls off (2,671 tokens, 32/32,
+// 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
+// Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
+// the backward.
+constexpr int64_t kSelfShort = 512;
+SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
+  SelfCfg c = {false, 1, 0, 0, 0, 0};
+  const bool varlen = is_varlen(op);
+  const bool f32 = d.dtype == BS_F32;  // dK/dV's chains alone are split there, by the list
+  if ((f32 && k != kSelfDkdv) || (varlen && (nseg < 1 || (!f32 && nseg > kSelfMaxSegs)))) return c;
+  PlanCfg cfg[2];
+  plans_of(op, d, cfg);
+  const bool dkdv = k == kSelfDkdv;
+  const int64_t slots = dkdv ? 256 : 512;
+  c.items = max_items_of(cfg[dkdv ? 1 : 0], d, nseg, varlen);
+  const int64_t wgs = c.wgs = c.items * (dkdv ? d.hkv : d.hq);
+  const int64_t len = dkdv ? d.total_q : d.total_k;
+  const int64_t longest = varlen && max_seqlen < len ? max_seqlen : len;
+  const bool more = !f32 && longest <= kSelfShort;
+  if (wgs < 1 || (more ? 2 * wgs >= 3 * slots : wgs > slots)) return c;
+  c.self = !f32;
+  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim);
+  const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
+  const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)
+                 : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
+  const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
+  const size_t slab = rows * (d.head_dim + (k == kSelfFwd ? 2 : 0)) * sizeof(float);
+  if (rows == 0) return c;  // no output rows (all segments lack queries, or keys): nothing to share
+  const size_t limit = k == kSelfFwd ? kFewBytes : (size_t)64 << 20;
+  for (int32_t s = 1; s <= 8 && s <= chain && (s == 1 || s * slab <= limit); ++s) {
+    const double cost = (double)((wgs * s + slots - 1) / slots) * chain / s * t +
+                        (s > 1 ? 5 + 2e-6 * (double)(s * slab) / 3 : 0);
+    if (s == 1 || cost < c.us) {
+      c.us = cost;
+      c.splits = s;
+    }
+  }
+  c.bytes = c.splits > 1 ? align256(c.splits * slab) : 0;
+  return c;
+}
+
 // Whether a varlen forward takes the few-query kernel, from the sizes alone, and its buffers.
 //
 // The rule compares two estimates in microseconds (segments taken as equally long), fitted to
-// both kernels at 1..64 segments of 1..512 queries over 300..16K keys, MHA and GQA:
+// 1,400 calls of 1..64 segments of 1..512 queries over 100..16K keys, MHA and GQA:
 //   few-query: 4, +5 for the merge, 4 per row block that a workgroup starts on average, and the
 //     larger of the key bytes at 5.3 TB/s (a third of that again for each further row block
 //     that reads them) and 1.6 per 128 keys of a 32-row block, shared evenly by 512 workgroups
 //     unless the bound on a row's pieces leaves some of them idle;
-//   general:   5 for its plan, 8 per 512 workgroups (one for each 128-row tile of a head), and
-//     the larger of the key bytes at 3.9 TB/s and 0.84 per 128 keys of a workgroup, 256 at a
-//     time, the longest segment's in a row; 13 at least.
-// Measured on both sides, us (few / general; segments x queries, longest segment, heads):
-//   32x1 8K 64/8: 76 / 336    16x16 4K 64/8: 61 / 100    16x8 4K 32/32: 79 / 110
-//   4x32 4K 64/8: 27 / 31     4x64 4K 64/8: 39 / 32      1x256 8K 64/8: 65 / 55
-//   2x128 8K 32/32: 30 / 51   1x256 8K 8/8: 24 / 54      30x55 1.4K 16/16: 64 / 55
+//   general, self-planned: 6, 0.08 per segment, 1 per 128 workgroups beyond 256, and the larger of
+//     0.9 of that form's own estimate and the key bytes at 3.9 TB/s; 9.7 at least (below it the two
+//     are 1 to 3 us apart, and the smallest calls stay with few queries);
+//   general, by the list: 5 for its plan, and the larger of the key bytes at 3.9 TB/s and 8 per 512
+//     workgroups (one for each 128-row tile of a head) with 0.84 per 128 keys of a workgroup, 256
+//     at a time, the longest segment's in a row; 13 at least.
+// The choice is on average 2 % above the better of the two.  Measured on both sides, us
+// (few / general; segments x queries, longest segment, heads; head_dim 128):
+//   32x1 8K 64/8: 78 / 355    16x8 4K 32/32: 94 / 126    1x1 16K 64/8: 26 / 70
+//   4x1 1K 32/8: 12 / 14      70x1 139 12/2: 11 / 24     70x1 139 7/7: 14 / 15
+//   4x32 4K 64/8: 65 / 58     2x128 8K 32/32: 141 / 53   1x170 170 40/8: 15 / 9
+//   2 segments of 452 and 60, 8/8: 17 / 13   of 114 and 294, 16/16: 18 / 11   1x8 160 48/8: 11 / 7
 // and calls whose queries x heads leave room for fewer than two pieces per row (16 MiB, over
 // about 16K rows) stay on the general path.
-bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F) {
+bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F, const SelfCfg& self) {
   const double rows = (double)d.total_q * (d.hq / d.hkv), keys = (double)d.total_k / nseq / 128 + 1;
   const double rb = rows / 32 + nseq / 2 > nseq ? rows / 32 + nseq / 2 : nseq;
   const double mb = (double)d.total_k * d.hkv * d.head_dim * 4e-6;
@@ -204,9 +271,16 @@ bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& 
   const double few_c = 1.6 * keys * per_wg, few_m = mb / 5.3 * (1 + 0.35 * (rb / nseq - 1));
   const double few = 4 + (F.slabs > 1 ? 5 : 0) + 4 * per_wg +
                      (few_c > few_m ? few_c : few_m) * (F.per_min > blocks && blocks > 1 ? F.per_min / blocks : 1);
+  const double gen_m = mb / 3.9;
+  if (self.self) {
+    const double gen_c = 0.9 * self.us;
+    const double gen = 6 + 0.08 * nseq + (self.wgs > 256 ? (self.wgs - 256) / 128.0 : 0) +
+                       (gen_c > gen_m ? gen_c : gen_m);
+    return few < (gen > 9.7 ? gen : 9.7);
+  }
   const double wgs = ((double)d.total_q / 128 + nseq) * d.hq / 256, row = longest / 128.0;
-  const double gen_c = 0.84 * (wgs * keys > row ? wgs * keys : row), gen_m = mb / 3.9;
-  const double gen = 5 + 4 * wgs + (gen_c > gen_m ? gen_c : gen_m);
+  const double gen_c = 4 * wgs + 0.84 * (wgs * keys > row ? wgs * keys : row);
+  const double gen = 5 + (gen_c > gen_m ? gen_c : gen_m);
   return few < (gen > 13 ? gen : 13);
 }
 
@@ -233,72 +307,10 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
     F.part = F.stat + align256(sizeof(float) * 2 * (size_t)(rows * F.slabs));
     F.bytes = F.part + align256(sizeof(float) * (size_t)(rows * F.slabs * d.head_dim));
   }
-  if (!few_pays(d, nseq, longest, F)) return FewLayout{};
+  if (!few_pays(d, nseq, longest, F, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
   const int64_t wgs = line * d.hkv;
   F.blocks = wgs < 512 ? (int32_t)wgs : 512;  // two per CU
   return F;
-}
-
-// How a bf16 kernel of few workgroups runs: by its own plan (no list), each work item's chain of
-// tiles split over `splits` workgroups.
-struct SelfCfg {
-  bool self;
-  int32_t splits;
-  int64_t items;
-  size_t bytes;  // of the partials (0: none)
-};
-enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
-
-// The rule, from the sizes: at most as many workgroups as the chip holds at once (two per CU for
-// the forward and dQ, one for dK/dV), or less than half as many again where no segment is longer
-// than 512; and the number of parts (at most 8) with the smallest estimate in microseconds
-//   rounds of workgroups x chain / parts x t  +  (with parts) 5 for the second kernel and the
-//   partials' bytes, written and read, at 3 TB/s,
-// t = 0.65 per 64-key tile (forward), 0.9 (dQ), 1.9 per 96-row step (dK/dV; 1.2 per 64-row one;
-// float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.
-// Forward + backward, us, by the list / so:
-//   512 tokens, 8/8 heads: 55 / 49    505, 64/8: 99 / 68    628, 32/4: 134 / 70    864, 32/32: 61 / 56
-// and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
-// subsequences, 16/2 heads: 538 / 346.  Beyond the lines the gain falls off (2,671 tokens, 32/32,
-// 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
-// Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
-// the backward.
-constexpr int64_t kSelfShort = 512;
-SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
-  SelfCfg c = {false, 1, 0, 0};
-  const bool varlen = is_varlen(op);
-  const bool f32 = d.dtype == BS_F32;  // dK/dV's chains alone are split there, by the list
-  if ((f32 && k != kSelfDkdv) || (varlen && (nseg < 1 || (!f32 && nseg > kSelfMaxSegs)))) return c;
-  PlanCfg cfg[2];
-  plans_of(op, d, cfg);
-  const bool dkdv = k == kSelfDkdv;
-  const int64_t slots = dkdv ? 256 : 512;
-  c.items = max_items_of(cfg[dkdv ? 1 : 0], d, nseg, varlen);
-  const int64_t wgs = c.items * (dkdv ? d.hkv : d.hq);
-  const int64_t len = dkdv ? d.total_q : d.total_k;
-  const int64_t longest = varlen && max_seqlen < len ? max_seqlen : len;
-  const bool more = !f32 && longest <= kSelfShort;
-  if (wgs < 1 || (more ? 2 * wgs >= 3 * slots : wgs > slots)) return c;
-  c.self = !f32;
-  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim);
-  const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
-  const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)
-                 : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
-  const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
-  const size_t slab = rows * (d.head_dim + (k == kSelfFwd ? 2 : 0)) * sizeof(float);
-  if (rows == 0) return c;  // no output rows (all segments lack queries, or keys): nothing to share
-  const size_t limit = k == kSelfFwd ? kFewBytes : (size_t)64 << 20;
-  double best = 0;
-  for (int32_t s = 1; s <= 8 && s <= chain && (s == 1 || s * slab <= limit); ++s) {
-    const double cost = (double)((wgs * s + slots - 1) / slots) * chain / s * t +
-                        (s > 1 ? 5 + 2e-6 * (double)(s * slab) / 3 : 0);
-    if (s == 1 || cost < best) {
-      best = cost;
-      c.splits = s;
-    }
-  }
-  c.bytes = c.splits > 1 ? align256(c.splits * slab) : 0;
-  return c;
 }
 
 // Room beyond the plan and D.  A float32 backward asks for at least what the bf16 call of its

@@ -165,3 +165,20 @@ def test_noalloc_forward_rejects_sizes_beyond_its_scratch(lib):
     assert call(dims(head_dim=96)) == B.BS_ERR_UNSUPPORTED
     assert call(dims(), cu=None) == B.BS_ERR_INVALID_ARG
     assert call(dims(), n=-1) == B.BS_ERR_INVALID_ARG
+
+
+def test_few_query_forward_is_weighed_against_the_self_planned_one(lib):
+    """Which forward a call takes shows in its workspace: the packed op never takes the few-query
+    kernel and otherwise asks for the same.  Decoding takes it; short batches of self-attention,
+    which the self-planned kernel does in one launch, and long chains that it splits, do not."""
+    def few(total_q, total_k, hq, hkv, n, longest):
+        d = dims(total_q=total_q, total_k=total_k, hq=hq, hkv=hkv)
+        a, b = (B.bs_attn_workspace_size(op, d, n, longest)
+                for op in (B.BS_OP_VARLEN_FWD, B.BS_OP_PACKED_CHUNK_FWD))
+        return a != b
+    assert few(32, 100000, 64, 8, 32, 8192)
+    assert few(1, 16384, 64, 8, 1, 16384)
+    assert few(70, 4900, 12, 2, 70, 139)
+    for call in ((512, 512, 8, 8, 2, 452), (408, 408, 16, 16, 2, 294), (454, 454, 12, 4, 4, 197),
+                 (170, 170, 40, 8, 1, 170), (256, 14012, 32, 32, 2, 8192)):
+        assert not few(*call), call

@@ -57,6 +57,29 @@ def test_few_queries_match_oracle(gpu, shape, hq, hkv, d, causal):
     assert torch.equal(lse.view(torch.int32), got["pieces"][1].view(torch.int32))
 
 
+@pytest.mark.parametrize("n", [257, 1023, 1024, 1025])
+def test_many_sequences(gpu, n):
+    """Sequences beyond the first wave of the table, and a full table of 1024 (1025: the general
+    path); some without keys or queries."""
+    hq, hkv, d, sc = 2, 1, 64, scale_for(64)
+    rng = np.random.default_rng(n)
+    lk = [int(x) for x in rng.integers(0, 60, n)]
+    lq = [int(x) for x in rng.integers(0, 3, n)]
+    lk[0], lk[255], lk[256], lk[n - 1], lq[n - 1], lq[n // 2] = 0, 300, 0, 77, 1, 0
+    cq, ck = (torch.from_numpy(inputs.cu_seqlens(x)) for x in (lq, lk))
+    q, k, v, _ = make_qkv(37, sum(lq), sum(lk), hq, hkv, d, torch.bfloat16, with_do=False)
+    qg, kg, vg, cqg, ckg = to_gpu(q, k, v, cq, ck)
+    dims, mx = B.make_dims(qg, kg), max(lq + lk)
+    few, general = (B.bs_attn_workspace_size(op, dims, n, mx)
+                    for op in (B.BS_OP_VARLEN_FWD, B.BS_OP_PACKED_CHUNK_FWD))
+    assert (few != general) == (n <= 1024)
+    out, lse = torch.full_like(qg, 7.0), torch.full((hq, sum(lq)), 7.0, device=gpu)
+    B.bs_attn_varlen_fwd(qg, kg, vg, cqg, ckg, mx, True, sc, out=out, lse=lse)
+    o_ref, lse_ref = A.varlen_fwd(q, k, v, cq.numpy(), ck.numpy(), True, sc)
+    check_close("O", f64(out), o_ref, BF["o"], bf16_out=True)
+    check_lse("LSE", f64(lse), lse_ref, BF["lse"])
+
+
 def test_few_queries_bad_cu_seqlens_writes_nothing(gpu):
     q, k, v, _ = make_qkv(14, 4, 900, 8, 2, 128, torch.bfloat16, with_do=False)
     qg, kg, vg = to_gpu(q, k, v)
