@@ -51,7 +51,7 @@ void dq_bf16_kernel(const BwdParams p) {
     slab = b - i * p.self.splits;
     if (!self_plan(p.self.plan, p.causal, kPlanFwd, BM, BN, i, pl, it)) return;
   } else {
-    if (!block_work(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
+    if (!block_work<true>(blockIdx.x, p.hdr, p.items, p.hq, p.group, 0, it, h)) return;
   }
   const int hk = h / p.group;
 
