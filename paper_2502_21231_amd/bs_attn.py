@@ -129,8 +129,9 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(t: torch.Tensor) -> int:
-    """Handle of the current stream of the tensor's device."""
-    if _raw_stream is not None:
+    """Handle of the current stream of the tensor's device (ValueError for a tensor on the host, whose
+    device index would name the current GPU to the internal call)."""
+    if _raw_stream is not None and t.is_cuda:
         return _raw_stream(t.get_device())
     return torch.cuda.current_stream(t.device).cuda_stream
 
