@@ -162,9 +162,9 @@ def _need(t: torch.Tensor, name: str, dtype=None, ndim=None) -> None:
 
 
 def make_dims(q: torch.Tensor, k: torch.Tensor | None) -> bs_dims:
-    tq, hq, d = q.shape
+    qs = q.shape
     tk, hkv = k.shape[:2] if k is not None else (0, 1)
-    return bs_dims(tq, tk, hq, hkv, d, _dtype_code(q))
+    return bs_dims(qs[0], tk, qs[1], hkv, qs[2], _dtype_code(q))
 
 
 def bs_attn_workspace_size(op: int, dims: bs_dims, num_seqs: int = 1, max_seqlen: int = 0) -> int:
