@@ -110,10 +110,22 @@ def test_chunk_without_queries_or_keys(gpu, tq, tk):
 
 @pytest.mark.parametrize("hq,hkv", [(16, 16), (16, 4), (24, 8)])
 def test_several_heads_per_xcd(gpu, hq, hkv):
-    """Head counts that are multiples of 8: each of the 8 XCDs owns hq/8 query heads (hkv/8 KV
-    heads in dK/dV, when that divides), interleaved item by item along each segment's run of
-    the work list; ragged segments, an empty one and a single token."""
+    """Head counts that are multiples of 8 on grids that plan for themselves (below the lines of
+    the rule): each of the 8 XCDs owns hq/8 query heads (hkv/8 KV heads in dK/dV, when that
+    divides) or the heads go round; ragged segments, an empty one and a single token."""
     run_varlen([300, 1, 770, 0, 64, 129], hq, hkv, 128, torch.bfloat16, seed=8)
+
+
+@pytest.mark.parametrize("hq,hkv,d,long", [(16, 16, 128, 6), (24, 8, 128, 6), (16, 4, 64, 14), (12, 6, 64, 9)])
+def test_several_heads_per_xcd_by_the_list(gpu, hq, hkv, d, long):
+    """The same through the work list (more workgroups than the chip holds at once, segments beyond
+    512): hq/8 heads of each XCD one after another (16/16), or interleaved because they share a K/V
+    stream (24/8, 16/4), dK/dV with and without a multiple of 8, and neither (12/6)."""
+    lens = [300, 1, 770, 0, 64, 129] + [520] * long
+    items = -(-sum(lens) // 128) + len(lens)
+    # the rules of the forward, dQ and dK/dV (at least half again the slots would do without a long one)
+    assert max(lens) > 512 and items * hq > 512 and items * hkv > 256
+    run_varlen(lens, hq, hkv, d, torch.bfloat16, seed=8)
 
 
 def test_varlen_q_shorter_than_k_bottom_right(gpu):
