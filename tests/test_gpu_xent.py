@@ -33,9 +33,10 @@ def check_row_results(name, loss, lse, dz, z_cpu, y_cpu, g, ignore_index, bf16):
                                        (21, 16392), (12, 65536), (7, 131072), (5, 131080),
                                        (6, 152064)])
 def test_xent_matches_oracle(gpu, dtype, rows, vocab):
-    """bf16: the register-resident form for vocab multiples of 8 in (16384, 131072] with 4, 8 and
-    16 chunks per lane (16392, 65536, 128256, 131072), the streamed form beyond it (131080,
-    152064) and below it (1000); float32 always streams.  Element path for vocab 7, 32003 and 1.
+    """Rows in registers at 256 lanes x 2 chunks (1, 7, 1000), 512 x 8 (bf16 16392 and 32003), 1024
+    x 8 (bf16 65536, float32 16392 and 32003) and 1024 x 16 (bf16 128256 and 131072, float32
+    65536), the form that reads what does not fit there twice (the rest), and rows of odd length,
+    whose entries before and after the 16-byte chunks are held one per lane (1, 7, 32003).
     Labels at both ends of the vocabulary, ignored rows, token-level scale 1/rows."""
     z, y = inputs.xent_inputs(7, rows, vocab, dtype=dtype, ignore_every=8)
     y[0] = 0
