@@ -105,9 +105,18 @@ enum {
 };
 
 /* Bytes of workspace that `op` needs for these sizes (num_seqs, max_seqlen are
- * ignored by the two single-chunk ops).  Calls of few workgroups ask for room for partial
- * results too (16 MiB at most forward, 64 MiB backward); with a workspace that holds the plan
- * (and, backward, D) but not that room they run without it, slower.  Returns 0 when the arguments are invalid (then
+ * ignored by the two single-chunk ops).  Besides what it must have (the plan and, backward, D) a
+ * call asks for room that makes it faster:
+ *   - bf16 calls of few workgroups, and the float32 dK/dV, for partial results (16 MiB at most
+ *     forward, 64 MiB backward);
+ *   - other bf16 backwards of up to 1,024 segments for a second header and work list (256 B and 48 B
+ *     per 128-key tile), so that one launch plans both;
+ *   - float32 backwards for at least what the bf16 call of the same sizes asks for, and float32
+ *     bs_attn_varlen_bwd for 4 total_q hq head_dim bytes that it must be given (no kernel uses
+ *     them now).
+ * A workspace without that optional room is accepted; the call is then slower, and since its sums
+ * run in another order its results can differ in the last bits from those with the room.  The same
+ * sizes with the same workspace size give the same bits.  Returns 0 when the arguments are invalid (then
  * bs_last_error() says why).  The workspace needs no initialisation and holds
  * nothing across calls except what bs_read_device_status() reads. */
 size_t bs_attn_workspace_size(int op, const bs_dims* dims, int32_t num_seqs, int32_t max_seqlen);
@@ -127,7 +136,8 @@ int bs_attn_varlen_fwd(const bs_dims* dims, const void* q, const void* k, const 
 
 /* Bytes of the per-device scratch array behind bs_attn_varlen_fwd_noalloc(). */
 #define BS_NOALLOC_SCRATCH_BYTES ((size_t)4 << 20)
-/* ... and of what follows it there: the partial results of calls of few queries per segment. */
+/* ... and of what follows it there: partial results (calls of few queries per segment, chains of
+ * tiles that several workgroups share). */
 #define BS_NOALLOC_PIECE_BYTES ((size_t)16 << 20)
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
@@ -135,8 +145,8 @@ int bs_attn_varlen_fwd(const bs_dims* dims, const void* q, const void* k, const 
  * workspace arguments.  Same computation, arguments, layouts and results as
  * bs_attn_varlen_fwd; the plan that the forward kernel walks goes into a file-scope
  * device array of BS_NOALLOC_SCRATCH_BYTES (4 MiB), followed by BS_NOALLOC_PIECE_BYTES
- * (16 MiB), that the library holds on every device it runs on until the process ends.  No hipMalloc or hipFree, and no allocating
- * library routine, is called.
+ * (16 MiB), that the library holds on every device it runs on until the process ends.  No
+ * hipMalloc or hipFree, and no allocating library routine, is called.
  *   - Limit: the plan takes 256 B + 4 (2 num_seqs + 3) B (each part rounded up to 256 B)
  *     + 48 B per work item, with ceil(total_q / 128) + num_seqs items (bf16) or
  *     ceil(total_q / 64) + num_seqs items (float32); sizes beyond the array return
@@ -325,7 +335,9 @@ int bs_attn_plan_export(int op, const bs_dims* dims, const int32_t* cu_seqlens_q
 
 /* Kernel classes timed by the profiling hooks below. */
 enum {
-  BS_KERNEL_PLAN = 0,       /* the three planning kernels of a plan */
+  BS_KERNEL_PLAN = 0,       /* one entry per planning step: one launch (up to 1,024 segments; of
+                             * a backward often both lists) or three; none in calls whose
+                             * kernels plan for themselves */
   BS_KERNEL_FWD = 1,        /* forward attention kernel */
   BS_KERNEL_PREPROCESS = 2, /* none (D = rowsum(dO * O) is formed by the dQ kernels) */
   BS_KERNEL_BWD_DQ = 3,     /* backward kernel producing dQ */

@@ -61,7 +61,8 @@ constexpr int kHeadMajorRowsDkdv = 16384;
 // The item is read beside the list's length, except with kCountFirst, where it is read after it: on
 // long chunks that small difference in when workgroups start decides how far apart those that share
 // a K/V stream drift (a 32K-token query chunk against 32K-key chunks, 32/32 heads, HBM reads per
-// launch, beside / after: dQ 8.6 / 6.4 GB, forward 6.5 / 7.6 GB).
+// launch over several GPUs, beside / after: dQ 8.5 to 9.3 / 6.4 GB, forward 6.4 to 7.6 / 7.4 to 10.7,
+// dK/dV 4.7 / 4.7; dQ 20.92 / 20.61 ms).
 template <bool kCountFirst = false>
 __device__ __forceinline__ bool block_work(int b, const WsHeader* __restrict__ hdr,
                                            const WorkItem* __restrict__ items, int n_heads,

@@ -357,8 +357,8 @@ WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   if (is_bwd(op)) {
     L.dvec = off;
     off += align256(sizeof(float) * (size_t)(d.hq * d.total_q));
-    // the float32 varlen backward's size has room for a dQ accumulator (unused: its dQ kernel
-    // writes dq itself, as the bf16 one does)
+    // the size of the float32 varlen backward has room for a dQ accumulator, as callers were told
+    // before its dQ kernel wrote dq itself; nothing uses it
     if (writes_dq(op) && d.dtype == BS_F32)
       off += align256(sizeof(float) * (size_t)(d.total_q * d.hq * d.head_dim));
   }

@@ -19,8 +19,9 @@
 //
 // Measured at 2,048 tokens in 5 segments, 8/4 heads, head_dim 64, against one thread per row
 // on the vector unit before: forward 1,010 -> 35 us, dQ 880 -> 49 us, dK/dV 2,300 -> 84 us
-// (28, 43 and 57 us at the library product's rate); error of dK against float64 7.4e-7 ->
-// 4.8e-7.  At 4,096 tokens, 32/8 heads, head_dim 128: 126 -> 2.5 ms for the three.  Few key tiles
+// (10, 15 and 19 us of useful FLOP at the library product's rate: one segment holds half of the
+// tokens, and the kernels wait for its chains of up to eight 128-row tiles); error of dK against
+// float64 7.4e-7 -> 4.8e-7.  At 4,096 tokens, 32/8 heads, head_dim 128: 126 -> 2.5 ms for the three.  Few key tiles
 // (a rule in capi.hip): several workgroups share a dK/dV item (751 tokens, 16/2 heads: 329 -> 165
 // us forward + backward).
 //
