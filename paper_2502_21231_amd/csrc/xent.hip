@@ -346,14 +346,24 @@ __global__ __launch_bounds__(kStreamThreads) void xent_stream_kernel(const XentP
     }
     T* dr = static_cast<T*>(p.dlogits) + row * p.vocab;
     const float g = p.grad_scale;
-    for (c = tid; c < p.vocab; c += NT) {
-      float v = 0.f;
-      if (!ignored) {
-        v = fast_exp2(fmaf((float)zr[c], kLog2e, -lse2)) * g;
-        if (c == y) v -= g;
-      }
-      dr[c] = narrow<T>(v);
+    if (ignored) {
+      for (c = tid; c < p.vocab; c += NT) dr[c] = narrow<T>(0.f);
+      continue;
     }
+    auto grad = [&](float z, int64_t at) {
+      const float v = fast_exp2(fmaf(z, kLog2e, -lse2)) * g;
+      dr[at] = narrow<T>(at == y ? v - g : v);
+    };
+    // U loads in flight here too (one at a time: 89 us instead of 51 at 100 x 200,003 bf16, 89
+    // instead of 63 at 1,000 x 50,257)
+    for (c = tid; c + (U - 1) * NT < p.vocab; c += U * NT) {
+      float z[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) z[u] = (float)zr[c + u * NT];
+#pragma unroll
+      for (int u = 0; u < U; ++u) grad(z[u], c + u * NT);
+    }
+    for (; c < p.vocab; c += NT) grad((float)zr[c], c);
   }
 }
 
