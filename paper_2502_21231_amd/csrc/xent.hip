@@ -139,10 +139,10 @@ __device__ __forceinline__ void stream_tail(const typename XVec<T>::type* src, i
 
 // Waves per SIMD: at up to 8 chunks per lane (64 registers) the CU's 2,048 lanes are filled.
 constexpr int xent_waves(int cpt) { return cpt <= 8 ? 8 : 4; }
-constexpr int xent_blocks_per_cu(int nt, int cpt) { return xent_waves(cpt) * 256 / nt; }
+constexpr int xent_blocks_per_cu(int nt, int waves) { return waves * 256 / nt; }
 
-template <typename T, int NT, int CPT, bool kTail>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(xent_waves(CPT))))
+template <typename T, int NT, int CPT, bool kTail, int kWaves>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kWaves)))
 void xent_kernel(const XentParams p, int64_t rows) {
   constexpr int N = XVec<T>::N, NW = NT / 64;
   typedef typename XVec<T>::type V;
@@ -354,8 +354,8 @@ __global__ __launch_bounds__(kStreamThreads) void xent_stream_kernel(const XentP
       const float v = fast_exp2(fmaf(z, kLog2e, -lse2)) * g;
       dr[at] = narrow<T>(at == y ? v - g : v);
     };
-    // U loads in flight here too (one at a time: 89 us instead of 51 at 100 x 200,003 bf16, 89
-    // instead of 63 at 1,000 x 50,257)
+    // U loads in flight here too (one at a time / so: 100 x 200,003 bf16 89 / 38 us, 1,000 x 50,257
+    // 89 / 50; float32 92 / 46 and 125 / 101)
     for (c = tid; c + (U - 1) * NT < p.vocab; c += U * NT) {
       float z[U];
 #pragma unroll
@@ -381,10 +381,19 @@ hipError_t launch_xent(const XentParams& p, int64_t rows, hipStream_t stream) {
     hipLaunchKernelGGL(xent_stream_kernel<T>, blocks(1), dim3(kStreamThreads), 0, stream, p, rows);
     return hipGetLastError();
   }
-#define BS_XENT(NT, CPT, TAIL)                                                              \
-  hipLaunchKernelGGL((xent_kernel<T, NT, CPT, TAIL>), blocks(xent_blocks_per_cu(NT, CPT)),  \
+#define BS_XENT_W(NT, CPT, TAIL, WAVES)                                                         \
+  hipLaunchKernelGGL((xent_kernel<T, NT, CPT, TAIL, WAVES>), blocks(xent_blocks_per_cu(NT, WAVES)), \
                      dim3(NT), 0, stream, p, rows)
+#define BS_XENT(NT, CPT, TAIL) BS_XENT_W(NT, CPT, TAIL, xent_waves(CPT))
   const int64_t nch = p.vocab / XVec<T>::N;  // chunks of a row at most
+  // a long bf16 row for at most every other CU: no row overlaps another, and what counts is one
+  // workgroup's work per entry, which streaming needs less of (64 x 200,000 with / without the
+  // gradient: 27.3 / 13.8 us by the forms below, 24.9 / 13.0 so; 200 x 152,064: 26.9 / 13.4 below)
+  if constexpr (sizeof(T) == 2)
+    if (nch > 16384 && rows * 2 <= cus) {
+      BS_XENT_W(1024, 3, true, 4);
+      return hipGetLastError();
+    }
   if (nch <= 512) BS_XENT(256, 2, false);
   else if (nch <= 2048) BS_XENT(256, 8, false);
   else if (nch <= 4096) BS_XENT(512, 8, false);
@@ -395,6 +404,7 @@ hipError_t launch_xent(const XentParams& p, int64_t rows, hipStream_t stream) {
   else if (nch <= 16384) BS_XENT(1024, 16, false);
   else BS_XENT(1024, 16, true);
 #undef BS_XENT
+#undef BS_XENT_W
   return hipGetLastError();
 }
 
