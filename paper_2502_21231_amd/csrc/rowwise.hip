@@ -24,7 +24,7 @@ template <> __device__ __forceinline__ float from_f<float>(float x) { return x; 
 // sets (the steps of a context-parallel ring):
 //   LSE = m + log(sum_c exp(LSE_c - m)),   O = sum_c exp(LSE_c - LSE) O_c,
 // m = max_c LSE_c; partials at -inf weigh 0; all -inf gives O = 0, LSE = -inf.
-template <typename T, int D, int U>
+template <typename T, int D, int U, bool kByXcd>
 __global__ __launch_bounds__(256) void lse_merge_kernel(const T* __restrict__ parts,
                                                         const float* __restrict__ lse_parts,
                                                         int32_t n, int64_t rows, int32_t hq,
@@ -32,11 +32,11 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const T* __restrict__ pa
                                                         float* __restrict__ lse) {
   typedef typename Vec<T>::type V;
   constexpr int LPR = D / Vec<T>::N;  // lanes per row
-  // Blocks are dealt to the 8 XCDs round-robin; each XCD takes a contiguous eighth of the rows,
-  // so that a line of the LSE (one head, 32 tokens) comes into one XCD's L2, not into eight
-  // (bf16, n = 8, 8,192 tokens, 32 heads: 108.2 -> 103.4 us, 5.9 TB/s; n = 2, 48 heads: 55.7 ->
-  // 49.8).
-  const int64_t blk = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  // Blocks are dealt to the 8 XCDs round-robin; with kByXcd each XCD takes a contiguous eighth of
+  // the rows, so that a line of the LSE (one head, 32 tokens) comes into one XCD's L2, not into
+  // eight (bf16, n = 8, 8,192 tokens, 32 heads: 108.2 -> 103.4 us, 5.9 TB/s; n = 2, 48 heads: 55.7 ->
+  // 49.8).  The rule and where it does not pay are at the launch.
+  const int64_t blk = kByXcd ? (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
   const int64_t gid = blk * blockDim.x + threadIdx.x;
   const int64_t row = gid / LPR;      // row = t * hq + h
   const int part = gid % LPR;
@@ -209,20 +209,27 @@ hipError_t launch_lse_merge(const bs_dims& dims, const void* out_parts, const fl
   if (rows == 0) return hipSuccess;
   const int vec = dims.dtype == BS_BF16 ? 8 : 4;
   const unsigned grid = (blocks_for(rows * (dims.head_dim / vec)) + 7) / 8 * 8;
-#define BS_MERGE_U(T, D, U)                                                                   \
-  hipLaunchKernelGGL((lse_merge_kernel<T, D, U>), dim3(grid), dim3(256), 0, stream,          \
+  // rows of 512 bytes, 64K of them or more: the lines of the LSE are then little of the traffic, and
+  // eight streams far apart cost more (float32, head_dim 128, round / by XCD: n = 2, 8,192 tokens, 32
+  // heads 62.4 / 65.8 us; n = 8, 4,096 tokens 98.3 / 101.4; n = 16, 1,024 tokens, 16 heads 23.4 / 22.2;
+  // head_dim 64, n = 4, 16,384 tokens, 8 heads 28.7 / 27.0)
+  const bool by_xcd = rows < 65536;
+#define BS_MERGE_U(T, D, U, X)                                                                \
+  hipLaunchKernelGGL((lse_merge_kernel<T, D, U, X>), dim3(grid), dim3(256), 0, stream,       \
                      static_cast<const T*>(out_parts), lse_parts, n, rows, dims.hq,           \
                      dims.total_q, static_cast<T*>(out), lse)
-#define BS_MERGE(T, D)                                                                        \
+#define BS_MERGE(T, D, X)                                                                     \
   do {                                                                                        \
-    if (n <= 2) BS_MERGE_U(T, D, 2);                                                          \
-    else if (n <= 4) BS_MERGE_U(T, D, 4);                                                     \
-    else BS_MERGE_U(T, D, 8);                                                                 \
+    if (n <= 2) BS_MERGE_U(T, D, 2, X);                                                       \
+    else if (n <= 4) BS_MERGE_U(T, D, 4, X);                                                  \
+    else BS_MERGE_U(T, D, 8, X);                                                              \
   } while (0)
   if (dims.dtype == BS_BF16) {
-    if (dims.head_dim == 128) BS_MERGE(bf16, 128); else BS_MERGE(bf16, 64);
+    if (dims.head_dim == 128) BS_MERGE(bf16, 128, true); else BS_MERGE(bf16, 64, true);
+  } else if (dims.head_dim == 64) {
+    BS_MERGE(float, 64, true);
   } else {
-    if (dims.head_dim == 128) BS_MERGE(float, 128); else BS_MERGE(float, 64);
+    if (by_xcd) BS_MERGE(float, 128, true); else BS_MERGE(float, 128, false);
   }
 #undef BS_MERGE
 #undef BS_MERGE_U
