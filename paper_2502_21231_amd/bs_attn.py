@@ -131,8 +131,9 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 def _stream(t: torch.Tensor) -> int:
     """Handle of the current stream of the tensor's device (ValueError for a tensor on the host, whose
     device index would name the current GPU to the internal call)."""
-    if _raw_stream is not None and t.is_cuda:
-        return _raw_stream(t.get_device())
+    index = t.get_device()
+    if _raw_stream is not None and index >= 0:
+        return _raw_stream(index)
     return torch.cuda.current_stream(t.device).cuda_stream
 
 
