@@ -205,7 +205,9 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 // Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
 // the backward.
 constexpr int64_t kSelfShort = 512;
-SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
+// seen: queries or keys that the longest chain walks at most, where that is known.
+SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen,
+                 int64_t seen = INT64_MAX) {
   SelfCfg c = {false, 1, 0, 0, 0, 0};
   const bool varlen = is_varlen(op);
   const bool f32 = d.dtype == BS_F32;  // dK/dV's chains alone are split there, by the list
@@ -221,8 +223,8 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
   const bool more = !f32 && longest <= kSelfShort;
   if (wgs < 1 || (more ? 2 * wgs >= 3 * slots : wgs > slots)) return c;
   c.self = !f32;
-  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim);
-  const double chain = dkdv ? (double)((longest + bm - 1) / bm * (d.hq / d.hkv)) : longest / 64.0;
+  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim), walk = longest < seen ? longest : seen;
+  const double chain = dkdv ? (double)((walk + bm - 1) / bm * (d.hq / d.hkv)) : walk / 64.0;
   const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)
                  : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
   const size_t rows = dkdv ? (size_t)(2 * d.total_k * d.hkv) : (size_t)(d.total_q * d.hq);
@@ -238,6 +240,24 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
     }
   }
   c.bytes = c.splits > 1 ? align256(c.splits * slab) : 0;
+  return c;
+}
+
+// The form of one call.  A causal chunk's offsets tell how long its chains are at most, and so
+// whether sharing them pays (they do not change which form the sizes ask for, nor its room).  A
+// 326-query chunk whose keys of 5,463 it sees the first 326 of, 32/4 heads, forward: in 4 parts 24 us,
+// unsplit 11.
+SelfCfg self_cfg_at(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen,
+                    int64_t q_off, int64_t k_off, int causal) {
+  SelfCfg c = self_cfg(k, op, d, nseg, max_seqlen);
+  if (c.splits == 1 || is_varlen(op) || !causal) return c;
+  // key j visible to query i iff j <= i + diag: query tiles see total_q + diag keys at most, key
+  // tiles are seen from query -diag on
+  int64_t diag = q_off - k_off;
+  diag = diag < -kDiagClamp ? -kDiagClamp : (diag > kDiagClamp ? kDiagClamp : diag);
+  const int64_t seen = k != kSelfDkdv ? d.total_q + diag : (diag < 0 ? d.total_q + diag : d.total_q);
+  const int32_t splits = self_cfg(k, op, d, nseg, max_seqlen, seen > 0 ? seen : 0).splits;
+  if (splits < c.splits) c.splits = splits;
   return c;
 }
 
@@ -402,8 +422,8 @@ hipError_t run_plan(int op, const bs_dims& d, int i, const int32_t* cu_q, const 
 const SelfPlan* self_plan_of(SelfKernel k, int op, const bs_dims& d, const int32_t* cu_q,
                              const int32_t* cu_k, const int64_t* q_pos, const int64_t* k_pos,
                              int32_t num_seqs, int32_t max_seqlen, int64_t q_off, int64_t k_off,
-                             void* ws, void* buf, SelfPlan* sp) {
-  const SelfCfg c = self_cfg(k, op, d, is_varlen(op) ? num_seqs : 1, max_seqlen);
+                             int causal, void* ws, void* buf, SelfPlan* sp) {
+  const SelfCfg c = self_cfg_at(k, op, d, is_varlen(op) ? num_seqs : 1, max_seqlen, q_off, k_off, causal);
   if (!c.self) return nullptr;
   const int64_t diag = q_off - k_off;
   PlanArgs& a = sp->plan;
@@ -493,7 +513,7 @@ int fwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   SelfPlan sp;
   void* buf = pieces != nullptr ? pieces : (ws_bytes >= L.total ? static_cast<char*>(ws) + L.extra : nullptr);
   const SelfPlan* self = self_plan_of(kSelfFwd, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen,
-                                      q_off, k_off, ws, buf, &sp);
+                                      q_off, k_off, causal, ws, buf, &sp);
   if (self == nullptr) {
     ProfScope ps(BS_KERNEL_PLAN, s);
     BS_HIP(run_plan(op, d, 0, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
@@ -544,7 +564,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   SelfPlan sp;
   void* buf = ws_bytes >= L.total ? base + L.extra : nullptr;
   const SelfPlan* self = self_plan_of(kSelfDq, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen,
-                                      q_off, k_off, ws, buf, &sp);
+                                      q_off, k_off, causal, ws, buf, &sp);
   const WsHeader* hdr = static_cast<const WsHeader*>(ws);
   // both lists by one launch where neither kernel plans for itself and there is room for two
   PlanCfg cfg[2];
@@ -576,7 +596,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
              "dQ sum launch");
   }
   self = self_plan_of(kSelfDkdv, op, d, cu_q, cu_k, q_pos, k_pos, num_seqs, max_seqlen, q_off, k_off,
-                      ws, buf, &sp);
+                      causal, ws, buf, &sp);
   Lp = L;
   const void* list = ws;
   if (both) {
@@ -592,7 +612,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   {
     ProfScope ps(BS_KERNEL_BWD_DKDV, s);
     if (f32) {
-      const SelfCfg c = self_cfg(kSelfDkdv, op, d, nseg, max_seqlen);
+      const SelfCfg c = self_cfg_at(kSelfDkdv, op, d, nseg, max_seqlen, q_off, k_off, causal);
       const int32_t splits = buf != nullptr ? c.splits : 1;
       float* part = static_cast<float*>(buf);
       BS_HIP(launch_dkdv_f32(d, q, k, v, dout, lse, dvec, causal, scale, dk, dv, kv_accumulate, ws,

@@ -118,6 +118,14 @@ def test_split_chunks_fold_and_accumulate(gpu, d, tq, tk, diag):
         check_close(name, f64(g), np.asarray(r) + 0.5, BF["grad"])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tq,tk,diag", [(326, 2463, 0), (379, 1569, -127), (200, 900, -500), (1500, 400, -1300)])
+def test_split_chunks_that_see_few_keys(gpu, d, tq, tk, diag):
+    """Chunks whose offsets hide most keys (all of them in the third): fewer parts than the room
+    in the workspace is for."""
+    test_split_chunks_fold_and_accumulate(gpu, d, tq, tk, diag)
+
+
 @pytest.mark.parametrize("n", [65, 255, 256, 257])
 def test_many_segments(gpu, n):
     """Segments beyond the first wave, and a full table of 256 (257: by the list), empty ones and
