@@ -111,10 +111,9 @@ enum {
  *     forward, 64 MiB backward);
  *   - other bf16 backwards of up to 1,024 segments for a second header and work list (256 B and 48 B
  *     per 128-key tile), so that one launch plans both;
- *   - float32 backwards for at least what the bf16 call of the same sizes asks for, and float32
- *     bs_attn_varlen_bwd for 4 total_q hq head_dim bytes that it must be given (no kernel uses
- *     them now).
- * A workspace without that optional room is accepted; the call is then slower, and since its sums
+ *   - float32 backwards for at least what the bf16 call of the same sizes asks for.
+ * (float32 bs_attn_varlen_bwd must be given 4 total_q hq head_dim bytes for a dq that overlaps an
+ * input.)  A workspace without that optional room is accepted; the call is then slower, and since its sums
  * run in another order its results can differ in the last bits from those with the room.  The same
  * sizes with the same workspace size give the same bits.  Returns 0 when the arguments are invalid (then
  * bs_last_error() says why).  The workspace needs no initialisation and holds
@@ -166,7 +165,8 @@ int bs_attn_varlen_fwd_noalloc(const bs_dims* dims, const void* q, const void* k
 
 /* Varlen backward: given the forward's out and lse and the upstream gradient
  * dout, writes dq [T, hq, d], dk and dv [Tk, hkv, d] (overwritten, not added).
- * Every gradient is accumulated in float32 and rounded once. */
+ * Every gradient is accumulated in float32 and rounded once.  A float32 dq may overlap the inputs
+ * (dq == q, say); a bfloat16 one may not overlap q, k, v, dout or lse. */
 int bs_attn_varlen_bwd(const bs_dims* dims, const void* q, const void* k, const void* v,
                        const void* out, const float* lse, const void* dout,
                        const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k,
@@ -342,7 +342,7 @@ enum {
   BS_KERNEL_PREPROCESS = 2, /* none (D = rowsum(dO * O) is formed by the dQ kernels) */
   BS_KERNEL_BWD_DQ = 3,     /* backward kernel producing dQ */
   BS_KERNEL_BWD_DKDV = 4,   /* backward kernel producing dK and dV */
-  BS_KERNEL_FINALIZE = 5,   /* float32 dQ accumulator -> dq */
+  BS_KERNEL_FINALIZE = 5,   /* float32 dQ accumulator or workspace -> dq */
   BS_KERNEL_MERGE = 6,      /* LSE merge */
   BS_KERNEL_XENT = 7,       /* softmax cross-entropy */
   BS_KERNEL_COUNT = 8

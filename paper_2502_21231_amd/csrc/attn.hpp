@@ -293,6 +293,7 @@ struct WsLayout {
   size_t seg_dst;     // int32[num_seqs]
   size_t sorted;      // WorkItem[max_items]
   size_t dvec;        // float[hq * T]      (backward: rowsum(dO * O))
+  size_t dq_late;     // float[T * hq * d]  (float32 varlen backward: dq that lies over an input)
   size_t extra;       // pieces of the few-query forward, or partials of split chains: optional
   size_t total;
   int64_t max_items;

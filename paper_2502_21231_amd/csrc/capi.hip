@@ -377,10 +377,10 @@ WsLayout layout_of(int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen) {
   if (is_bwd(op)) {
     L.dvec = off;
     off += align256(sizeof(float) * (size_t)(d.hq * d.total_q));
-    // the size of the float32 varlen backward has room for a dQ accumulator, as callers were told
-    // before its dQ kernel wrote dq itself; nothing uses it
-    if (writes_dq(op) && d.dtype == BS_F32)
+    if (writes_dq(op) && d.dtype == BS_F32) {  // (bwd_common says when it is used)
+      L.dq_late = off;
       off += align256(sizeof(float) * (size_t)(d.total_q * d.hq * d.head_dim));
+    }
   }
   L.extra = off;
   L.total = off + extra_bytes(op, d, nseg, max_seqlen);
@@ -560,6 +560,13 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   char* base = static_cast<char*>(ws);
   float* dvec = reinterpret_cast<float*>(base + L.dvec);
   const bool f32 = d.dtype == BS_F32;
+  // A float32 varlen dq may take the place of an input (dq == q, a reused buffer): the kernels that
+  // follow the dQ kernel still read that, so dq is written last, from the workspace.
+  auto over = [&](const void* x, int64_t n) { return overlaps(dq, qn * 4, x, n * 4); };
+  const bool late = f32 && direct && (over(q, qn) || over(k, kn) || over(v, kn) || over(out, qn) ||
+                                      over(dout, qn) || over(lse, d.total_q * d.hq));
+  float* dq_late = reinterpret_cast<float*>(base + L.dq_late);
+  void* dq_to = late ? dq_late : (direct ? dq : dq_accum);
   WsLayout Lp = L;
   SelfPlan sp;
   void* buf = ws_bytes >= L.total ? base + L.extra : nullptr;
@@ -583,8 +590,7 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
   {
     ProfScope ps(BS_KERNEL_BWD_DQ, s);
     if (f32)
-      BS_HIP(launch_dq_f32(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : dq_accum,
-                           !direct, ws, Lp, s),
+      BS_HIP(launch_dq_f32(d, q, k, v, out, dout, lse, dvec, causal, scale, dq_to, !direct, ws, Lp, s),
              "backward dQ launch");
     else
       BS_HIP(launch_dq_bf16(d, q, k, v, out, dout, lse, dvec, causal, scale, direct ? dq : nullptr,
@@ -630,6 +636,10 @@ int bwd_common(int op, const bs_dims* dims, const void* q, const void* k, const 
                                 kv_accumulate ? kSumAddF32 : kSumBf16, hdr, s),
                "dK/dV sum launch");
     }
+  }
+  if (late) {
+    ProfScope ps(BS_KERNEL_FINALIZE, s);
+    BS_HIP(launch_sum_slabs(dq_late, 1, qn, dq, nullptr, kSumF32, hdr, s), "dQ copy launch");
   }
   return ok();
 }

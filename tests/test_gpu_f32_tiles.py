@@ -74,3 +74,29 @@ def test_f32_split_dkdv(gpu, d, hq, hkv, causal):
         got = B.bs_attn_varlen_bwd(qg, kg, vg, og, lg, dog, cug, cug, 500, causal, sc, workspace=ws)
         for name, g, r in zip(("dQ", "dK", "dV"), got, want):
             check_close(name, f64(g), r, 1e-5, rel=1e-5)
+
+
+@pytest.mark.parametrize("over", ["q", "k", "v", "out", "do", "shifted"])
+def test_f32_dq_over_an_input(gpu, over):
+    """dq in the place of an input, whole or shifted by some rows into a buffer that both share: the
+    gradients of separate buffers, and nothing written where cu_seqlens is rejected."""
+    lens, h, d, sc = [150, 0, 33, 257], 4, 64, scale_for(64)
+    T, mx = sum(lens), max(lens)
+    cu = torch.from_numpy(inputs.cu_seqlens(lens)).cuda()
+    q, k, v, do = to_gpu(*make_qkv(25, T, T, h, h, d, torch.float32))
+    out, lse = B.bs_attn_varlen_fwd(q, k, v, cu, cu, mx, True, sc)
+    want = B.bs_attn_varlen_bwd(q, k, v, out, lse, do, cu, cu, mx, True, sc)
+    t = {"q": q, "k": k, "v": v, "out": out, "do": do}
+    if over == "shifted":
+        both = torch.empty(T + 40, h, d, device=gpu)
+        t["q"], dq = both[40:], both[:T]
+        t["q"].copy_(q)
+    else:
+        dq = t[over]
+    def bwd(c):
+        return B.bs_attn_varlen_bwd(t["q"], t["k"], t["v"], t["out"], lse, t["do"], c, c, mx, True, sc, dq=dq)
+    kept = dq.clone()
+    bwd(torch.tensor([0, 10, 5, 20, T], dtype=torch.int32, device=gpu))
+    assert torch.equal(dq, kept)
+    for g, r in zip(bwd(cu), want):
+        assert torch.equal(g, r)
