@@ -115,7 +115,7 @@ enum {
  * (float32 bs_attn_varlen_bwd must be given 4 total_q hq head_dim bytes for a dq that overlaps an
  * input.)  A workspace without that optional room is accepted; the call is then slower, and since its sums
  * run in another order its results can differ in the last bits from those with the room.  The same
- * sizes with the same workspace size give the same bits.  Returns 0 when the arguments are invalid (then
+ * call with the same workspace size gives the same bits.  Returns 0 when the arguments are invalid (then
  * bs_last_error() says why).  The workspace needs no initialisation and holds
  * nothing across calls except what bs_read_device_status() reads. */
 size_t bs_attn_workspace_size(int op, const bs_dims* dims, int32_t num_seqs, int32_t max_seqlen);
