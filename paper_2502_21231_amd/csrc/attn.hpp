@@ -49,14 +49,14 @@ struct WsHeader {
 // on; the forward and dQ kernels do so for every segment.
 constexpr int kHeadMajorRowsDkdv = 16384;
 
-// Work item and head of block b of a grid of n_items * n_heads blocks; false when it has none.  Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), so with
-// n_heads a multiple of 8 each XCD owns the hx = n_heads / 8 heads x*hx .. x*hx+hx-1 and walks
-// the list segment by segment.  Inside a segment's run its heads are interleaved item by
-// item, except where the segment streams at least min_rows rows and the XCD's heads read
-// more than one stream (hx > heads_per_stream: heads that share a KV head share its K/V
-// stream): there the XCD walks one head's items at a time, so that the workgroups resident
-// on it read one stream, not hx / heads_per_stream, and each tile of it comes into the
-// XCD's L2 that many times less often.
+// Work item and head of block b of a grid of n_items * n_heads blocks; false when it has none.
+// Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), so with n_heads a
+// multiple of 8 each XCD owns the hx = n_heads / 8 heads x*hx .. x*hx+hx-1 and walks the list
+// segment by segment.  Inside a segment's run its heads are interleaved item by item, except where
+// the segment streams at least min_rows rows and the XCD's heads read more than one stream (hx >
+// heads_per_stream: heads that share a KV head share its K/V stream): there the XCD walks one
+// head's items at a time, so that the workgroups resident on it read one stream, not hx /
+// heads_per_stream, and each tile of it comes into the XCD's L2 that many times less often.
 //
 // The item is read beside the list's length, except with kCountFirst, where it is read after it: on
 // long chunks that small difference in when workgroups start decides how far apart those that share

@@ -13,7 +13,7 @@
 
 // Scratch of the allocation-free forward (bs_attn_varlen_fwd_noalloc): the plan that the
 // forward kernel walks (header, per-segment offsets, work list), then the pieces of the
-// few-query forward (kFewBytes).  Each device holds its own
+// few-query forward or the partials of split chains (kFewBytes).  Each device holds its own
 // copy from the time the library's code is loaded on it until the process ends.  Host code
 // never uses this name as an address: the device address comes from hipGetSymbolAddress.
 constexpr size_t kNoAllocScratchBytes = BS_NOALLOC_SCRATCH_BYTES;

@@ -12,8 +12,9 @@
 //     or 16.  A short row on 1024 lanes leaves the memory idle while its sums are combined;
 //     several small workgroups on a CU cover for one another.  Rows of 4,096 / 16,384 bf16
 //     entries (8,192 rows) ran at 1.3 / 2.7 TB/s on one 1024-lane workgroup per CU.
-//   - A row longer than 1024 x 16 chunks (131,072 bf16 entries) keeps that much in registers and
-//     reads the rest twice, the second time from the caches.
+//   - A row longer than 1024 x 16 chunks (131,072 bf16 entries) keeps that much in registers (3
+//     chunks per lane where rows are few: the rule is at the launch) and reads the rest twice,
+//     the second time from the caches.
 //   - Rows of any length and alignment: the chunks start at the row's first 16-byte boundary,
 //     and the up to 2 x (16 / size - 1) entries before and after them are held one per lane.
 //     (One entry per lane and load, as odd vocabularies went before, ran at 1.9 TB/s at 2,048 x
