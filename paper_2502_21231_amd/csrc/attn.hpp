@@ -519,10 +519,15 @@ struct FewLayout {
   size_t part, stat;  // offsets in buf of the pieces' sums and statistics (counts come first)
   size_t bytes;       // 0: the call does not take this path
   int32_t slabs;      // pieces of a row at most; 1: no row has two
-  int32_t per_min;    // key blocks per workgroup at least
+  int32_t per_min;    // key blocks per workgroup at least (an estimate: the kernel finds its own)
   int32_t blocks;     // workgroups
 };
 constexpr int few_block_keys(int head_dim) { return head_dim == 128 ? 128 : 256; }
+// Key blocks per workgroup with which rows of up to nkb blocks have at most `slabs` > 1 pieces (at
+// most ceil(nkb / per) + 1 of them).
+__host__ __device__ constexpr int32_t few_per_min(int32_t nkb, int32_t slabs) {
+  return nkb > 1 ? (nkb + slabs - 2) / (slabs - 1) : 1;
+}
 hipError_t launch_few_fwd(const bs_dims& dims, const void* q, const void* k, const void* v,
                           const int32_t* cu_q, const int32_t* cu_k, int32_t num_seqs,
                           int32_t max_seqlen, int causal, float scale, void* out, float* lse,

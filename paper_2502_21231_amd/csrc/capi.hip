@@ -199,12 +199,21 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 // float32: 7.5 per 128-row step, 3.8 at head_dim 64), the measured times of a chain on a CU.
 // Forward + backward, us, by the list / so:
 //   512 tokens, 8/8 heads: 55 / 49    505, 64/8: 99 / 68    628, 32/4: 134 / 70    864, 32/32: 61 / 56
-// and a 1,018-token ring of three steps, 8/8 heads: 407 / 369; a 4-way zig-zag step of short
-// subsequences, 16/2 heads: 538 / 346.  Beyond the lines the gain falls off (2,671 tokens, 32/32,
+// and a 1,018-token ring of three steps, 8/8 heads: 415 / 347 to 388; a 4-way zig-zag share of 1,240,
+// 480 and 2,000 tokens, 16/2 heads: 896 / 505 (head_dim 64: 692 / 382).  Beyond the lines the gain falls off (2,671 tokens, 32/32,
 // 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
 // Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
 // the backward.
 constexpr int64_t kSelfShort = 512;
+
+// The longest segment that the estimates count on: max_seqlen is only a bound (a context's or a
+// buffer's length, say), so at most four times the mean.  With the bound itself, 2,660 tokens in 32
+// segments of up to 139, 4/1 heads, max_seqlen 2,660, forward: 55 us (four parts of chains of two
+// tiles); so 11.
+int64_t likely_longest(int64_t bound, int64_t total, int64_t nseg) {
+  const int64_t four = nseg > 4 ? 4 * ((total + nseg - 1) / nseg) : total;
+  return bound < four ? bound : four;
+}
 // seen: queries or keys that the longest chain walks at most, where that is known.
 SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t max_seqlen,
                  int64_t seen = INT64_MAX) {
@@ -223,7 +232,8 @@ SelfCfg self_cfg(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_t m
   const bool more = !f32 && longest <= kSelfShort;
   if (wgs < 1 || (more ? 2 * wgs >= 3 * slots : wgs > slots)) return c;
   c.self = !f32;
-  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim), walk = longest < seen ? longest : seen;
+  const int64_t likely = likely_longest(longest, len, varlen ? nseg : 1);
+  const int64_t bm = f32 ? kF32BwdBM : bwd_bm(d.head_dim), walk = likely < seen ? likely : seen;
   const double chain = dkdv ? (double)((walk + bm - 1) / bm * (d.hq / d.hkv)) : walk / 64.0;
   const double t = f32 ? (d.head_dim == 128 ? 7.5 : 3.8)
                  : dkdv ? (d.head_dim == 128 ? 1.9 : 1.2) : (k == kSelfFwd ? 0.65 : 0.9);
@@ -313,21 +323,21 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
   const int64_t line = (d.total_q * group / 32 + nseq) * (d.total_k / blk + nseq);
   if (line >= (int64_t(1) << 31)) return F;
   const int64_t longest = max_seqlen < d.total_k ? max_seqlen : d.total_k;
-  const int64_t nkb = (longest + blk - 1) / blk;  // key blocks of a segment at most
-  if (nkb <= 1) {
+  const int64_t likely = likely_longest(longest, d.total_k, nseq);
+  if (longest <= blk) {  // one key block per segment at most
     F.slabs = F.per_min = 1;
     F.bytes = 256;
-  } else {  // a row's pieces: at most ceil(nkb / per) + 1
+  } else {
     const size_t row_bytes = (size_t)(d.head_dim + 2) * sizeof(float);
     F.stat = align256(sizeof(int32_t) * (size_t)rows);
     if (F.stat + 512 + 2 * (size_t)rows * row_bytes > kFewBytes) return FewLayout{};
     const size_t fit = (kFewBytes - F.stat - 512) / ((size_t)rows * row_bytes);
     F.slabs = fit < kFewSlabs ? (int32_t)fit : kFewSlabs;
-    F.per_min = (int32_t)((nkb + F.slabs - 2) / (F.slabs - 1));
+    F.per_min = few_per_min((int32_t)((likely + blk - 1) / blk), F.slabs);
     F.part = F.stat + align256(sizeof(float) * 2 * (size_t)(rows * F.slabs));
     F.bytes = F.part + align256(sizeof(float) * (size_t)(rows * F.slabs * d.head_dim));
   }
-  if (!few_pays(d, nseq, longest, F, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
+  if (!few_pays(d, nseq, likely, F, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
   const int64_t wgs = line * d.hkv;
   F.blocks = wgs < 512 ? (int32_t)wgs : 512;  // two per CU
   return F;

@@ -182,3 +182,16 @@ def test_few_query_forward_is_weighed_against_the_self_planned_one(lib):
     for call in ((512, 512, 8, 8, 2, 452), (408, 408, 16, 16, 2, 294), (454, 454, 12, 4, 4, 197),
                  (170, 170, 40, 8, 1, 170), (256, 14012, 32, 32, 2, 8192)):
         assert not few(*call), call
+
+
+def test_short_segments_are_not_split_for_a_loose_max_seqlen(lib):
+    """max_seqlen is only a bound (a buffer's or a context's length): 32 segments of 83 tokens on
+    average ask for the room of unsplit chains whatever it says, as with their exact maximum."""
+    d = dims(total_q=2660, total_k=2660, hq=4, hkv=1)
+    size = lambda op, mx: B.bs_attn_workspace_size(op, d, 32, mx)
+    for mx in (2660, 131072):
+        assert size(B.BS_OP_PACKED_CHUNK_FWD, mx) == size(B.BS_OP_PACKED_CHUNK_FWD, 139)
+    # one segment may be as long as its buffer: its chains are split
+    one = dims(total_q=2660, total_k=2660, hq=4, hkv=1)
+    assert (B.bs_attn_workspace_size(B.BS_OP_PACKED_CHUNK_FWD, one, 1, 131072)
+            > B.bs_attn_workspace_size(B.BS_OP_PACKED_CHUNK_FWD, one, 32, 131072))

@@ -125,3 +125,26 @@ def test_few_queries_graph_replays(gpu):
         assert torch.equal(out, want) and torch.equal(lse, want_l)
         o_ref, _ = A.varlen_fwd(q, k, v, cq.cpu().numpy(), inputs.cu_seqlens(lens), True, sc)
         check_close("O", f64(out), o_ref, BF["o"], bf16_out=True)
+
+
+def test_max_seqlen_far_above_the_lengths(gpu):
+    """max_seqlen is only a bound (a context's length): the pieces follow the longest segment that has
+    queries, as with the exact maximum, bit for bit."""
+    hq, hkv, d, sc = 32, 8, 128, scale_for(128)
+    lk = [int(x) for x in np.random.default_rng(3).integers(1, 700, 67)]
+    lk[5], lk[6] = 4000, 6000
+    lq = [1 + i % 3 for i in range(67)]
+    lq[6] = 0  # the longest has none
+    cq, ck = (torch.from_numpy(inputs.cu_seqlens(x)) for x in (lq, lk))
+    q, k, v, _ = make_qkv(38, sum(lq), sum(lk), hq, hkv, d, torch.bfloat16, with_do=False)
+    qg, kg, vg, cqg, ckg = to_gpu(q, k, v, cq, ck)
+    dims, got = B.make_dims(qg, kg), []
+    for mx in (max(lk), sum(lk), 131072):
+        sizes = [B.bs_attn_workspace_size(op, dims, 67, mx) for op in (B.BS_OP_VARLEN_FWD, B.BS_OP_PACKED_CHUNK_FWD)]
+        assert sizes[0] != sizes[1]  # this path
+        got.append(B.bs_attn_varlen_fwd(qg, kg, vg, cqg, ckg, mx, True, sc))
+    o_ref, lse_ref = A.varlen_fwd(q, k, v, cq.numpy(), ck.numpy(), True, sc)
+    check_close("O", f64(got[0][0]), o_ref, BF["o"], bf16_out=True)
+    check_lse("LSE", f64(got[0][1]), lse_ref, BF["lse"])
+    for out, lse in got[1:]:
+        assert torch.equal(out, got[0][0]) and torch.equal(lse, got[0][1])
