@@ -201,7 +201,8 @@ struct PlanArgs {
 };
 // LDS of self_plan.
 struct SelfLds {
-  uint2 seg[kSelfMaxSegs];  // size (len_q + len_k) and items of each segment
+  __attribute__((aligned(16))) uint2 seg[kSelfMaxSegs];  // size (len_q + len_k) and items of each segment
+  uint32_t at[kSelfMaxSegs];  // slots before it
   int32_t bad, n;
   int32_t found, slot;  // the segment of item i, and its first slot
 };
@@ -245,7 +246,11 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
     it = make_item(s, 0, kind == kPlanFwd ? n - 1 - i : i, causal, kind, tile_a, tile_b, 0, n);
     return true;
   }
-  if (tid == 0) lds.bad = BS_DEV_OK;
+  if (tid == 0) {
+    lds.bad = BS_DEV_OK;
+    lds.n = 0;
+  }
+  if (tid < kSelfMaxSegs) lds.at[tid] = 0;
   __syncthreads();
   uint2 mine = {0, 0};
   if (tid < a.num_seqs) {
@@ -253,24 +258,45 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
     if (s.lq < 0 || s.lk < 0) atomicCAS(&lds.bad, 0, BS_DEV_NOT_MONOTONE);
     else if (s.lq > a.max_seqlen || s.lk > a.max_seqlen) atomicCAS(&lds.bad, 0, BS_DEV_TOO_LONG);
     else mine = {(uint32_t)(s.lq + s.lk), (uint32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a)};
-    lds.seg[tid] = mine;
   }
+  if (tid < kSelfMaxSegs) lds.seg[tid] = mine;
   if (tid == 0) {
     if (a.cu_q[0] != 0 || a.cu_k[0] != 0) atomicExch(&lds.bad, BS_DEV_BAD_FIRST);
     else if (a.cu_q[a.num_seqs] != a.total_q || a.cu_k[a.num_seqs] != a.total_k)
       atomicExch(&lds.bad, BS_DEV_BAD_TOTAL);
   }
   __syncthreads();
-  if (tid < kSelfMaxSegs) {  // slots before this segment: one broadcast read per segment
-    uint32_t at = 0, n = 0;
-#pragma unroll 4
-    for (int j = 0; j < a.num_seqs; ++j) {
-      const uint2 o = lds.seg[j];
-      n += o.y;
-      at += o.x > mine.x || (o.x == mine.x && j < tid) ? o.y : 0;
+  // Slots before each segment: each wave compares 64 segments with a part of the table, eight at a
+  // time so that their (broadcast) reads are under way together.  107 segments of 240 tokens on
+  // average, 2/2 heads, head_dim 64, forward: 28 us one by one and every wave all of the table, so 15.
+  {
+    const int groups = (a.num_seqs + 63) >> 6, parts = (int)(blockDim.x >> 6) / groups;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), g = w % groups, part = w / groups;
+    const int len = ((a.num_seqs + parts - 1) / parts + 7) & ~7;
+    if (part < parts) {
+      const int b = g * 64 + (tid & 63);
+      const uint32_t size = lds.seg[b].x;
+      uint32_t at = 0, n = 0;
+      const int end = min(a.num_seqs, (part + 1) * len);
+      for (int j = part * len; j < end; j += 8) {  // entries past num_seqs are empty
+        uint4 o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(lds.seg)[(j >> 1) + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // equal sizes in their own order
+          n += o[u].y + o[u].w;
+          at += o[u].x + (j + 2 * u < b ? 1u : 0u) > size ? o[u].y : 0u;
+          at += o[u].z + (j + 2 * u + 1 < b ? 1u : 0u) > size ? o[u].w : 0u;
+        }
+      }
+      atomicAdd(&lds.at[b], at);
+      if (b == 0) atomicAdd(&lds.n, (int32_t)n);
     }
-    if (tid == 0) lds.n = (int32_t)n;
-    if (tid < a.num_seqs && (uint32_t)i - at < mine.y) {  // (at most one segment)
+  }
+  __syncthreads();
+  if (tid < a.num_seqs) {
+    const uint32_t at = lds.at[tid];
+    if ((uint32_t)i - at < mine.y) {  // (at most one segment)
       lds.found = tid;
       lds.slot = (int32_t)at;
     }
