@@ -190,6 +190,11 @@ __device__ __forceinline__ WorkItem make_item(const Seg& s, int32_t b, int64_t t
 // holds at once (about: the rule is in capi.hip): a workgroup reads cu_seqlens about as fast as a
 // work item.
 constexpr int kSelfMaxSegs = 256;
+// Up to so many segments are walked in the planner's order; more of them, as they are stored: each is
+// then short, and ranking them costs more than the order gives (forward, us, ranked / as stored: 238
+// segments of one query over 179 keys on average, 1/1 heads, 15.0 / 10.8; 107 segments, 25.7K tokens, 2/2
+// heads, head_dim 64: 15.0 / 15.4).
+constexpr int kSelfRankSegs = 64;
 struct PlanArgs {
   const int32_t* cu_q;  // NULL: one chunk with diagonal diag_chunk
   const int32_t* cu_k;
@@ -201,10 +206,10 @@ struct PlanArgs {
 };
 // LDS of self_plan.
 struct SelfLds {
-  __attribute__((aligned(16))) uint2 seg[kSelfMaxSegs];  // size (len_q + len_k) and items of each segment
-  uint32_t at[kSelfMaxSegs];  // slots before it
+  __attribute__((aligned(16))) uint2 seg[kSelfRankSegs];  // size (len_q + len_k) and items of each segment
+  uint32_t at[kSelfRankSegs];  // slots before it (more segments: items of each wave's)
   int32_t bad, n;
-  int32_t found, slot;  // the segment of item i, and its first slot
+  int32_t found, slot, items;  // the segment of item i, its first slot and its items
 };
 
 // Head and list slot (x splits) of block b.  With `own` (and n_heads a multiple of 8) each XCD owns
@@ -226,9 +231,9 @@ __device__ __forceinline__ int self_block(int b, int n_heads, bool own, int& hea
   return i;
 }
 
-// Item i of the list, in the planner's order (larger segments first, a segment's longest chains
-// first), for a workgroup of at least kSelfMaxSegs threads; false when there is none or cu_seqlens
-// is rejected.  The order matters on grids that the chip holds at once too: it decides which
+// Item i of the list, in the planner's order (larger segments first up to kSelfRankSegs of them, a
+// segment's longest chains first), for a workgroup of at least kSelfMaxSegs threads; false when
+// there is none or cu_seqlens is rejected.  The order matters on grids that the chip holds at once too: it decides which
 // workgroups share a CU (forward, us, planning launch and list / segments and tiles as they come /
 // in order: 300 queries each over 2.3K and 6.3K keys, 48/8 heads, head_dim 64, 74 / 84 / 70; 4,096
 // tokens, 12/4, head_dim 64, 54 / 57 / 49).  Block 0 writes the header.
@@ -250,7 +255,7 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
     lds.bad = BS_DEV_OK;
     lds.n = 0;
   }
-  if (tid < kSelfMaxSegs) lds.at[tid] = 0;
+  if (tid < kSelfRankSegs) lds.at[tid] = 0;
   __syncthreads();
   uint2 mine = {0, 0};
   if (tid < a.num_seqs) {
@@ -259,45 +264,58 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
     else if (s.lq > a.max_seqlen || s.lk > a.max_seqlen) atomicCAS(&lds.bad, 0, BS_DEV_TOO_LONG);
     else mine = {(uint32_t)(s.lq + s.lk), (uint32_t)(((kind == kPlanFwd ? s.lq : s.lk) + tile_a - 1) / tile_a)};
   }
-  if (tid < kSelfMaxSegs) lds.seg[tid] = mine;
+  if (tid < kSelfRankSegs) lds.seg[tid] = mine;
   if (tid == 0) {
     if (a.cu_q[0] != 0 || a.cu_k[0] != 0) atomicExch(&lds.bad, BS_DEV_BAD_FIRST);
     else if (a.cu_q[a.num_seqs] != a.total_q || a.cu_k[a.num_seqs] != a.total_k)
       atomicExch(&lds.bad, BS_DEV_BAD_TOTAL);
   }
   __syncthreads();
-  // Slots before each segment: each wave compares 64 segments with a part of the table, eight at a
-  // time so that their (broadcast) reads are under way together.  107 segments of 240 tokens on
-  // average, 2/2 heads, head_dim 64, forward: 28 us one by one and every wave all of the table, so 15.
-  {
-    const int groups = (a.num_seqs + 63) >> 6, parts = (int)(blockDim.x >> 6) / groups;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), g = w % groups, part = w / groups;
-    const int len = ((a.num_seqs + parts - 1) / parts + 7) & ~7;
-    if (part < parts) {
-      const int b = g * 64 + (tid & 63);
-      const uint32_t size = lds.seg[b].x;
-      uint32_t at = 0, n = 0;
-      const int end = min(a.num_seqs, (part + 1) * len);
-      for (int j = part * len; j < end; j += 8) {  // entries past num_seqs are empty
-        uint4 o[4];
+  if (a.num_seqs <= kSelfRankSegs) {
+    // slots before each segment: each wave compares the segments with a part of the table, eight at a
+    // time so that their (broadcast) reads are under way together; entries past num_seqs are empty
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), b = tid & 63;
+    const int len = ((a.num_seqs - 1) / (int)(blockDim.x >> 6) + 8) & ~7;
+    const int end = min(a.num_seqs, (w + 1) * len);
+    const uint32_t size = lds.seg[b].x;
+    uint32_t at = 0, n = 0;
+    for (int j = w * len; j < end; j += 8) {
+      uint4 o[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(lds.seg)[(j >> 1) + u];
+      for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(lds.seg)[(j >> 1) + u];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {  // equal sizes in their own order
-          n += o[u].y + o[u].w;
-          at += o[u].x + (j + 2 * u < b ? 1u : 0u) > size ? o[u].y : 0u;
-          at += o[u].z + (j + 2 * u + 1 < b ? 1u : 0u) > size ? o[u].w : 0u;
-        }
+      for (int u = 0; u < 4; ++u) {  // equal sizes in their own order
+        n += o[u].y + o[u].w;
+        at += o[u].x + (j + 2 * u < b ? 1u : 0u) > size ? o[u].y : 0u;
+        at += o[u].z + (j + 2 * u + 1 < b ? 1u : 0u) > size ? o[u].w : 0u;
       }
-      atomicAdd(&lds.at[b], at);
-      if (b == 0) atomicAdd(&lds.n, (int32_t)n);
     }
-  }
-  __syncthreads();
-  if (tid < a.num_seqs) {
-    const uint32_t at = lds.at[tid];
-    if ((uint32_t)i - at < mine.y) {  // (at most one segment)
+    atomicAdd(&lds.at[b], at);
+    if (b == 0) atomicAdd(&lds.n, (int32_t)n);
+    __syncthreads();
+    if (tid < a.num_seqs && (uint32_t)i - lds.at[tid] < mine.y) {  // (at most one segment)
       lds.found = tid;
+      lds.items = (int32_t)mine.y;
+      lds.slot = (int32_t)lds.at[tid];
+    }
+  } else {  // as they are stored
+    uint32_t run = mine.y;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t x = __shfl_up(run, off);
+      run += (tid & 63) >= off ? x : 0;
+    }
+    if ((tid & 63) == 63) lds.at[tid >> 6] = run;
+    __syncthreads();
+    uint32_t at = run - mine.y, n = 0;
+    for (int w = 0; w < kSelfMaxSegs / 64; ++w) {
+      at += w < (tid >> 6) ? lds.at[w] : 0;
+      n += lds.at[w];
+    }
+    if (tid == 0) lds.n = (int32_t)n;
+    if (tid < a.num_seqs && (uint32_t)i - at < mine.y) {
+      lds.found = tid;
+      lds.items = (int32_t)mine.y;
       lds.slot = (int32_t)at;
     }
   }
@@ -308,7 +326,7 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
     a.hdr->n_items = code == BS_DEV_OK ? n : 0;
   }
   if (code != BS_DEV_OK || i >= n) return false;  // uniform
-  const int32_t b = lds.found, at = lds.slot, cnt = (int32_t)lds.seg[b].y;
+  const int32_t b = lds.found, at = lds.slot, cnt = lds.items;
   const Seg s = load_seg(a.cu_q, a.cu_k, a.q_pos, a.k_pos, b, a.total_q, a.total_k, 0);
   it = make_item(s, b, kind == kPlanFwd ? cnt - 1 - (i - at) : i - at, causal, kind, tile_a, tile_b, at, cnt);
   return true;
@@ -545,7 +563,7 @@ struct FewLayout {
   size_t part, stat;  // offsets in buf of the pieces' sums and statistics (counts come first)
   size_t bytes;       // 0: the call does not take this path
   int32_t slabs;      // pieces of a row at most; 1: no row has two
-  int32_t per_min;    // key blocks per workgroup at least (an estimate: the kernel finds its own)
+  int32_t per_min;    // key blocks per workgroup at least, if a segment may have max_seqlen keys
   int32_t blocks;     // workgroups
 };
 constexpr int few_block_keys(int head_dim) { return head_dim == 128 ? 128 : 256; }
