@@ -293,14 +293,16 @@ SelfCfg self_cfg_at(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_
 //   2 segments of 452 and 60, 8/8: 17 / 13   of 114 and 294, 16/16: 18 / 11   1x8 160 48/8: 11 / 7
 // and calls whose queries x heads leave room for fewer than two pieces per row (16 MiB, over
 // about 16K rows) stay on the general path.
-bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F, const SelfCfg& self) {
+// per_min: key blocks per workgroup at least, as expected.
+bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F, int32_t per_min,
+              const SelfCfg& self) {
   const double rows = (double)d.total_q * (d.hq / d.hkv), keys = (double)d.total_k / nseq / 128 + 1;
   const double rb = rows / 32 + nseq / 2 > nseq ? rows / 32 + nseq / 2 : nseq;
   const double mb = (double)d.total_k * d.hkv * d.head_dim * 4e-6;
   const double per_wg = rb * d.hkv / 512, blocks = per_wg * keys * 128 / few_block_keys(d.head_dim);
   const double few_c = 1.6 * keys * per_wg, few_m = mb / 5.3 * (1 + 0.35 * (rb / nseq - 1));
   const double few = 4 + (F.slabs > 1 ? 5 : 0) + 4 * per_wg +
-                     (few_c > few_m ? few_c : few_m) * (F.per_min > blocks && blocks > 1 ? F.per_min / blocks : 1);
+                     (few_c > few_m ? few_c : few_m) * (per_min > blocks && blocks > 1 ? per_min / blocks : 1);
   const double gen_m = mb / 3.9;
   if (self.self) {
     const double gen_c = 0.9 * self.us;
@@ -324,6 +326,7 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
   if (line >= (int64_t(1) << 31)) return F;
   const int64_t longest = max_seqlen < d.total_k ? max_seqlen : d.total_k;
   const int64_t likely = likely_longest(longest, d.total_k, nseq);
+  int32_t per_likely = 1;
   if (longest <= blk) {  // one key block per segment at most
     F.slabs = F.per_min = 1;
     F.bytes = 256;
@@ -333,11 +336,12 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
     if (F.stat + 512 + 2 * (size_t)rows * row_bytes > kFewBytes) return FewLayout{};
     const size_t fit = (kFewBytes - F.stat - 512) / ((size_t)rows * row_bytes);
     F.slabs = fit < kFewSlabs ? (int32_t)fit : kFewSlabs;
-    F.per_min = few_per_min((int32_t)((likely + blk - 1) / blk), F.slabs);
+    F.per_min = few_per_min((int32_t)((longest + blk - 1) / blk), F.slabs);
+    per_likely = few_per_min((int32_t)((likely + blk - 1) / blk), F.slabs);
     F.part = F.stat + align256(sizeof(float) * 2 * (size_t)(rows * F.slabs));
     F.bytes = F.part + align256(sizeof(float) * (size_t)(rows * F.slabs * d.head_dim));
   }
-  if (!few_pays(d, nseq, likely, F, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
+  if (!few_pays(d, nseq, likely, F, per_likely, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
   const int64_t wgs = line * d.hkv;
   F.blocks = wgs < 512 ? (int32_t)wgs : 512;  // two per CU
   return F;

@@ -46,6 +46,7 @@ struct FewParams {
   int32_t hq, hkv, group;
   int32_t causal;
   int32_t slabs;    // pieces of a row at most
+  int32_t per_min;  // blocks per workgroup that keep to it with a segment of max_seqlen keys
   float scale_log2;
 };
 
@@ -69,7 +70,7 @@ void few_fwd_kernel(const FewParams p) {
   __shared__ __attribute__((aligned(16))) bf16 Kt[4][KT * D];
   __shared__ __attribute__((aligned(16))) bf16 Vt[4][KT * D];
   __shared__ int32_t pre[kFewMaxSegs + 1];  // blocks before each segment, per KV head
-  __shared__ int32_t wsum[4], wmax[4];
+  __shared__ int32_t wsum[4];
   __shared__ int32_t bad;
   __shared__ float Ms[4][32], Ls[4][32];
 
@@ -78,6 +79,7 @@ void few_fwd_kernel(const FewParams p) {
   const int group = p.group;
 
   // the line of blocks: thread t takes segments 4t .. 4t+3
+  int32_t most = 0;  // key blocks of this thread's longest segment
   if (tid == 0) bad = 0;
   __syncthreads();
   {
@@ -88,7 +90,7 @@ void few_fwd_kernel(const FewParams p) {
       if (code != 0) atomicCAS(&bad, 0, code);
     }
     constexpr int PT = kFewMaxSegs / 256;
-    int32_t n[PT], sum = 0, most = 0;  // most: key blocks of the longest segment
+    int32_t n[PT], sum = 0;
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
       const int b = tid * PT + i;
@@ -111,14 +113,7 @@ void few_fwd_kernel(const FewParams p) {
       const int32_t x = __shfl_up(run, off);
       if (lane >= off) run += x;
     }
-    if (p.slabs > 1) {
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
-    }
-    if (lane == 63) {
-      wsum[w] = run;
-      wmax[w] = most;
-    }
+    if (lane == 63) wsum[w] = run;
     __syncthreads();
     int32_t at = run - sum;
     for (int i = 0; i < w; ++i) at += wsum[i];
@@ -139,11 +134,16 @@ void few_fwd_kernel(const FewParams p) {
   if (code != 0) return;  // uniform: nothing is written
   const int32_t line = pre[p.num_seqs];
   const int64_t all = (int64_t)line * p.hkv;
-  // (the longest segment, not max_seqlen, which is only a bound: 67 sequences of 1 to 20 queries over
-  // up to 651 keys, 32/8 heads, max_seqlen 26K: 100 us by the bound, 34 so)
-  const int32_t longest = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
-  const int32_t per_min = p.slabs > 1 ? few_per_min(longest, p.slabs) : 1;
-  const int32_t per = max((int32_t)((all + gridDim.x - 1) / gridDim.x), per_min);
+  int32_t per = (int32_t)((all + gridDim.x - 1) / gridDim.x);
+  if (per < p.per_min) {  // uniform
+    // by the longest segment, since max_seqlen is only a bound (67 sequences of 1 to 20 queries over up
+    // to 651 keys, 32/8 heads, max_seqlen 26K: 100 us by the bound, 34 so)
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
+    if (lane == 0) wsum[w] = most;
+    __syncthreads();
+    per = max(per, few_per_min(max(max(wsum[0], wsum[1]), max(wsum[2], wsum[3])), p.slabs));
+  }
   int64_t x = (int64_t)blockIdx.x * per;
   const int64_t x_end = min(all, x + per);
 
@@ -413,6 +413,7 @@ hipError_t launch_few_fwd(const bs_dims& dims, const void* q, const void* k, con
   p.group = dims.hq / dims.hkv;
   p.causal = causal;
   p.slabs = F.slabs;
+  p.per_min = F.per_min;
   p.scale_log2 = scale * kLog2e;
   const dim3 grid((unsigned)F.blocks), mgrid((unsigned)((dims.total_q * dims.hq * (dims.head_dim / 4) + 255) / 256));
   // keys read once (one row block per segment on average) go past the caches; where several row
