@@ -273,47 +273,62 @@ SelfCfg self_cfg_at(SelfKernel k, int op, const bs_dims& d, int64_t nseg, int64_
 
 // Whether a varlen forward takes the few-query kernel, from the sizes alone, and its buffers.
 //
-// The rule compares two estimates in microseconds (segments taken as equally long), fitted to
-// 1,400 calls of 1..64 segments of 1..512 queries over 100..16K keys, MHA and GQA:
-//   few-query: 4, +5 for the merge, 4 per row block that a workgroup starts on average, and the
-//     larger of the key bytes at 5.3 TB/s (a third of that again for each further row block
+// The rule compares two estimates in microseconds (segments taken as equally long), a pair of them for
+// each form that the general path would take, fitted to calls of MHA and GQA, training, prompts and
+// decoding, over up to 16K keys (self-planned: 1,400 of 1..64 segments, checked on 953 more of 1..256;
+// by the list: 2,000 of 1..1,024):
+//   self-planned: 6, 0.06 per segment and 1 per 128 workgroups beyond 256 (3.2 of these alone for
+//     segments as stored), and the larger of 0.9 of that form's own estimate and the key bytes at
+//     3.9 TB/s; 9.7 at least (below it the two are 1 to 3 us apart, and the smallest calls stay
+//     with few queries);
+//   few-query against it: 4, +5 for the merge, 4 per row block that a workgroup starts on average,
+//     and the larger of the key bytes at 5.3 TB/s (a third of that again for each further row block
 //     that reads them) and 1.6 per 128 keys of a 32-row block, shared evenly by 512 workgroups
 //     unless the bound on a row's pieces leaves some of them idle;
-//   general, self-planned: 6, 0.08 per segment, 1 per 128 workgroups beyond 256, and the larger of
-//     0.9 of that form's own estimate and the key bytes at 3.9 TB/s; 9.7 at least (below it the two
-//     are 1 to 3 us apart, and the smallest calls stay with few queries);
-//   general, by the list: 5 for its plan, and the larger of the key bytes at 3.9 TB/s and 8 per 512
-//     workgroups (one for each 128-row tile of a head) with 0.84 per 128 keys of a workgroup, 256
-//     at a time, the longest segment's in a row; 13 at least.
-// The choice is on average 2 % above the better of the two.  Measured on both sides, us
+//   by the list: 9.9, 0.13 per segment, and the larger of the key bytes at 5.6 TB/s and 2.6 + 1.28 per
+//     64-key tile for each round of 512 workgroups (one per 128-row tile of a head);
+//   few-query against it: 6.1, +4.6 for the merge, 2 and up to 1.7 more, by how full it is, for each
+//     row block that a workgroup starts, and the key bytes at 7 TB/s with 0.65 of that again for each
+//     further row block that reads them, longer where workgroups are idle.
+// The choice is on average 3.8 % and 0.2 % above the better of the two.  Measured on both sides, us
 // (few / general; segments x queries, longest segment, heads; head_dim 128):
 //   32x1 8K 64/8: 78 / 355    16x8 4K 32/32: 94 / 126    1x1 16K 64/8: 26 / 70
 //   4x1 1K 32/8: 12 / 14      70x1 139 12/2: 11 / 24     70x1 139 7/7: 14 / 15
 //   4x32 4K 64/8: 65 / 58     2x128 8K 32/32: 141 / 53   1x170 170 40/8: 15 / 9
 //   2 segments of 452 and 60, 8/8: 17 / 13   of 114 and 294, 16/16: 18 / 11   1x8 160 48/8: 11 / 7
+//   199x63 104 32/8: 145 / 112   114x1 79 64/64: 69 / 84   39x23 2.2K 16/16: 137 / 100
 // and calls whose queries x heads leave room for fewer than two pieces per row (16 MiB, over
 // about 16K rows) stay on the general path.
 // per_min: key blocks per workgroup at least, as expected.
-bool few_pays(const bs_dims& d, int64_t nseq, int64_t longest, const FewLayout& F, int32_t per_min,
-              const SelfCfg& self) {
-  const double rows = (double)d.total_q * (d.hq / d.hkv), keys = (double)d.total_k / nseq / 128 + 1;
-  const double rb = rows / 32 + nseq / 2 > nseq ? rows / 32 + nseq / 2 : nseq;
+bool few_pays(const bs_dims& d, int64_t nseq, const FewLayout& F, int32_t per_min, const SelfCfg& self) {
+  const double n = (double)nseq, group = (double)d.hq / d.hkv, lq = d.total_q / n, lk = d.total_k / n;
   const double mb = (double)d.total_k * d.hkv * d.head_dim * 4e-6;
-  const double per_wg = rb * d.hkv / 512, blocks = per_wg * keys * 128 / few_block_keys(d.head_dim);
-  const double few_c = 1.6 * keys * per_wg, few_m = mb / 5.3 * (1 + 0.35 * (rb / nseq - 1));
-  const double few = 4 + (F.slabs > 1 ? 5 : 0) + 4 * per_wg +
-                     (few_c > few_m ? few_c : few_m) * (per_min > blocks && blocks > 1 ? per_min / blocks : 1);
-  const double gen_m = mb / 3.9;
   if (self.self) {
-    const double gen_c = 0.9 * self.us;
-    const double gen = 6 + 0.08 * nseq + (self.wgs > 256 ? (self.wgs - 256) / 128.0 : 0) +
-                       (gen_c > gen_m ? gen_c : gen_m);
+    const double rows = d.total_q * group, keys = lk / 128 + 1;
+    const double rb = rows / 32 + nseq / 2 > n ? rows / 32 + nseq / 2 : n;
+    const double per_wg = rb * d.hkv / 512, blocks = per_wg * keys * 128 / few_block_keys(d.head_dim);
+    const double few_c = 1.6 * keys * per_wg, few_m = mb / 5.3 * (1 + 0.35 * (rb / n - 1));
+    const double few = 4 + (F.slabs > 1 ? 5 : 0) + 4 * per_wg +
+                       (few_c > few_m ? few_c : few_m) * (per_min > blocks && blocks > 1 ? per_min / blocks : 1);
+    const double gen_c = 0.9 * self.us, gen_m = mb / 3.9;
+    const double over = self.wgs > 256 ? (self.wgs - 256) / 128.0 : 0;
+    const double gen = 6 + (nseq <= kSelfRankSegs ? 0.06 * n + over : 3.2 * over) + (gen_c > gen_m ? gen_c : gen_m);
     return few < (gen > 9.7 ? gen : 9.7);
   }
-  const double wgs = ((double)d.total_q / 128 + nseq) * d.hq / 256, row = longest / 128.0;
-  const double gen_c = 4 * wgs + 0.84 * (wgs * keys > row ? wgs * keys : row);
-  const double gen = 5 + (gen_c > gen_m ? gen_c : gen_m);
-  return few < (gen > 13 ? gen : 13);
+  // tiles of a segment of on average x tiles: half a tile is lost, and no segment has less than one
+  auto whole = [](double x) { return x > 0.5 ? x + 0.5 : 1; };
+  // row blocks of a segment (a few queries on average are often one for most and many for some)
+  const double spread = 1 + 0.8 * (lq - 1) * group / 32, even = whole(lq * group / 32);
+  const double rb = even > spread ? even : spread, kb = whole(lk / few_block_keys(d.head_dim));
+  const double blocks = n * rb * kb * d.hkv / 512, least = blocks > 1 ? blocks : 1;
+  double per = ceil(blocks - 0.2);  // key blocks of a workgroup
+  if (per < per_min) per = per_min;
+  const double starts = per > kb ? per / kb : 1, full = lq * group / rb / 32;
+  const double few = 6.1 + (F.slabs > 1 ? 4.6 : 0) + starts * (2 + 1.7 * (full < 1 ? full : 1)) +
+                     mb / 7 * (1 + 0.65 * (rb - 1)) * (per_min > least ? per_min / least : 1);
+  const double rounds = n * whole(lq / 128) * d.hq / 512;
+  const double gen_c = (rounds > 1 ? rounds : 1) * (2.6 + 1.28 * (lk / 64 + 0.5)), gen_m = mb / 5.6;
+  return few < 9.9 + 0.13 * n + (gen_c > gen_m ? gen_c : gen_m);
 }
 
 FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen) {
@@ -341,7 +356,7 @@ FewLayout few_layout(int op, const bs_dims& d, int64_t nseq, int64_t max_seqlen)
     F.part = F.stat + align256(sizeof(float) * 2 * (size_t)(rows * F.slabs));
     F.bytes = F.part + align256(sizeof(float) * (size_t)(rows * F.slabs * d.head_dim));
   }
-  if (!few_pays(d, nseq, likely, F, per_likely, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
+  if (!few_pays(d, nseq, F, per_likely, self_cfg(kSelfFwd, op, d, nseq, max_seqlen))) return FewLayout{};
   const int64_t wgs = line * d.hkv;
   F.blocks = wgs < 512 ? (int32_t)wgs : 512;  // two per CU
   return F;

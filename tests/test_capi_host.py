@@ -195,3 +195,18 @@ def test_short_segments_are_not_split_for_a_loose_max_seqlen(lib):
     one = dims(total_q=2660, total_k=2660, hq=4, hkv=1)
     assert (B.bs_attn_workspace_size(B.BS_OP_PACKED_CHUNK_FWD, one, 1, 131072)
             > B.bs_attn_workspace_size(B.BS_OP_PACKED_CHUNK_FWD, one, 32, 131072))
+
+
+def test_many_short_segments_stay_with_the_list(lib):
+    """Batches of many short sequences, and prompts of tens of tokens, beyond the self-planned lines: the
+    few-query kernel would read their keys once per row block.  Decoding of as many takes it."""
+    def few(total_q, total_k, hq, hkv, n, longest, head_dim=128):
+        d = dims(total_q=total_q, total_k=total_k, hq=hq, hkv=hkv, head_dim=head_dim)
+        a, b = (B.bs_attn_workspace_size(op, d, n, longest)
+                for op in (B.BS_OP_VARLEN_FWD, B.BS_OP_PACKED_CHUNK_FWD))
+        return a != b
+    for call in ((7674, 7674, 32, 32, 126, 107), (12454, 12454, 32, 8, 199, 104), (9074, 9074, 64, 8, 178, 88, 64),
+                 (889, 54580, 16, 16, 39, 2193), (268, 21591, 32, 32, 16, 2119, 64)):
+        assert not few(*call), call
+    for call in ((114, 5380, 64, 64, 114, 79), (192, 10544, 64, 64, 192, 95), (344, 25356, 16, 8, 344, 120)):
+        assert few(*call), call
