@@ -272,31 +272,40 @@ __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kin
   }
   __syncthreads();
   if (a.num_seqs <= kSelfRankSegs) {
-    // slots before each segment: each wave compares the segments with a part of the table, eight at a
-    // time so that their (broadcast) reads are under way together; entries past num_seqs are empty
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), b = tid & 63;
-    const int len = ((a.num_seqs - 1) / (int)(blockDim.x >> 6) + 8) & ~7;
-    const int end = min(a.num_seqs, (w + 1) * len);
-    const uint32_t size = lds.seg[b].x;
+    // slots before segment b: the entries [j, end) of the table eight at a time, so that their
+    // (broadcast) reads are under way together; entries past num_seqs are empty
+    const int b = tid & 63;
     uint32_t at = 0, n = 0;
-    for (int j = w * len; j < end; j += 8) {
-      uint4 o[4];
+    auto rank = [&](int j, int end) {
+      const uint32_t size = lds.seg[b].x;
+      for (; j < end; j += 8) {
+        uint4 o[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(lds.seg)[(j >> 1) + u];
+        for (int u = 0; u < 4; ++u) o[u] = reinterpret_cast<const uint4*>(lds.seg)[(j >> 1) + u];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {  // equal sizes in their own order
-        n += o[u].y + o[u].w;
-        at += o[u].x + (j + 2 * u < b ? 1u : 0u) > size ? o[u].y : 0u;
-        at += o[u].z + (j + 2 * u + 1 < b ? 1u : 0u) > size ? o[u].w : 0u;
+        for (int u = 0; u < 4; ++u) {  // equal sizes in their own order
+          n += o[u].y + o[u].w;
+          at += o[u].x + (j + 2 * u < b ? 1u : 0u) > size ? o[u].y : 0u;
+          at += o[u].z + (j + 2 * u + 1 < b ? 1u : 0u) > size ? o[u].w : 0u;
+        }
       }
+    };
+    if (a.num_seqs <= 16) {  // one wave: sharing the table costs more (0.4 us at two segments)
+      if (tid < 64) rank(0, a.num_seqs);
+      if (tid == 0) lds.n = (int32_t)n;
+    } else {  // each wave a part of it
+      const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+      const int len = ((a.num_seqs - 1) / (int)(blockDim.x >> 6) + 8) & ~7;
+      rank(w * len, min(a.num_seqs, (w + 1) * len));
+      atomicAdd(&lds.at[b], at);
+      if (b == 0) atomicAdd(&lds.n, (int32_t)n);
+      __syncthreads();
+      at = lds.at[b];
     }
-    atomicAdd(&lds.at[b], at);
-    if (b == 0) atomicAdd(&lds.n, (int32_t)n);
-    __syncthreads();
-    if (tid < a.num_seqs && (uint32_t)i - lds.at[tid] < mine.y) {  // (at most one segment)
+    if (tid < a.num_seqs && (uint32_t)i - at < mine.y) {  // (at most one segment)
       lds.found = tid;
       lds.items = (int32_t)mine.y;
-      lds.slot = (int32_t)lds.at[tid];
+      lds.slot = (int32_t)at;
     }
   } else {  // as they are stored
     uint32_t run = mine.y;
