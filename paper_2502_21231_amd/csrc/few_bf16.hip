@@ -79,7 +79,6 @@ void few_fwd_kernel(const FewParams p) {
   const int group = p.group;
 
   // the line of blocks: thread t takes segments 4t .. 4t+3
-  int32_t most = 0;  // key blocks of this thread's longest segment
   if (tid == 0) bad = 0;
   __syncthreads();
   {
@@ -99,11 +98,7 @@ void few_fwd_kernel(const FewParams p) {
         const int64_t lq = (int64_t)p.cu_q[b + 1] - p.cu_q[b], lk = (int64_t)p.cu_k[b + 1] - p.cu_k[b];
         if (lq < 0 || lk < 0) atomicCAS(&bad, 0, BS_DEV_NOT_MONOTONE);
         else if (lq > p.max_seqlen || lk > p.max_seqlen) atomicCAS(&bad, 0, BS_DEV_TOO_LONG);
-        else if (lq > 0) {
-          const int32_t nkb = (int32_t)max((lk + BLK - 1) / BLK, (int64_t)1);
-          n[i] = (int32_t)((lq * group + 31) / 32 * nkb);
-          most = max(most, nkb);
-        }
+        else if (lq > 0) n[i] = (int32_t)((lq * group + 31) / 32 * max((lk + BLK - 1) / BLK, (int64_t)1));
       }
       sum += n[i];
     }
@@ -138,6 +133,9 @@ void few_fwd_kernel(const FewParams p) {
   if (per < p.per_min) {  // uniform
     // by the longest segment, since max_seqlen is only a bound (67 sequences of 1 to 20 queries over up
     // to 651 keys, 32/8 heads, max_seqlen 26K: 100 us by the bound, 34 so)
+    int32_t most = 0;
+    for (int b = tid; b < p.num_seqs; b += 256)
+      if (p.cu_q[b + 1] > p.cu_q[b]) most = max(most, (p.cu_k[b + 1] - p.cu_k[b] + BLK - 1) / BLK);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) most = max(most, __shfl_xor(most, off));
     if (lane == 0) wsum[w] = most;
