@@ -233,9 +233,9 @@ __device__ __forceinline__ int self_block(int b, int n_heads, bool own, int& hea
 
 // Item i of the list, in the planner's order (larger segments first up to kSelfRankSegs of them, a
 // segment's longest chains first), for a workgroup of at least kSelfMaxSegs threads; false when
-// there is none or cu_seqlens is rejected.  The order matters on grids that the chip holds at once too: it decides which
-// workgroups share a CU (forward, us, planning launch and list / segments and tiles as they come /
-// in order: 300 queries each over 2.3K and 6.3K keys, 48/8 heads, head_dim 64, 74 / 84 / 70; 4,096
+// there is none or cu_seqlens is rejected.  The order matters on grids that the chip holds at once
+// too: it decides which workgroups share a CU (forward, us, planning launch and list / segments and
+// tiles as they come / in order: 300 queries each over 2.3K and 6.3K keys, 48/8 heads, head_dim 64, 74 / 84 / 70; 4,096
 // tokens, 12/4, head_dim 64, 54 / 57 / 49).  Block 0 writes the header.
 __device__ __forceinline__ bool self_plan(const PlanArgs& a, int causal, int kind, int tile_a,
                                           int tile_b, int32_t i, SelfLds& lds, WorkItem& it) {

@@ -200,8 +200,8 @@ enum SelfKernel { kSelfFwd, kSelfDq, kSelfDkdv };
 // Forward + backward, us, by the list / so:
 //   512 tokens, 8/8 heads: 55 / 49    505, 64/8: 99 / 68    628, 32/4: 134 / 70    864, 32/32: 61 / 56
 // and a 1,018-token ring of three steps, 8/8 heads: 415 / 347 to 388; a 4-way zig-zag share of 1,240,
-// 480 and 2,000 tokens, 16/2 heads: 896 / 505 (head_dim 64: 692 / 382).  Beyond the lines the gain falls off (2,671 tokens, 32/32,
-// 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
+// 480 and 2,000 tokens, 16/2 heads: 896 / 505 (head_dim 64: 692 / 382).  Beyond the lines the gain
+// falls off (2,671 tokens, 32/32, 832 workgroups: 164 / 165; 1,875, 40/8, 800 workgroups: 171 / 168; 2,413, 32/32, 800: 184 / 176).
 // Partials: 16 MiB at most in the forward (what the allocation-free entry point holds), 64 MiB in
 // the backward.
 constexpr int64_t kSelfShort = 512;
